@@ -216,9 +216,11 @@ typedef struct {
                           kernel, 2 dataflow kernel (node state in registers) */
     int32_t wide;      /* with lanes = 64: how many of the heaviest nodes get a
                           wavefront (0 = chosen from the expected work) */
-    int32_t lattice;   /* wavefront-wide nodes: 0 auto (on when G marks both rates
-                          after either transition), 1 the same, 2 off (every
-                          step on one dependent chain); the results are equal */
+    int32_t lattice;   /* wavefront-wide nodes: 0 auto (windows of 64 steps at
+                          once when G marks both rates after either transition
+                          and no entry of S exceeds 2^20 in magnitude), 1 the
+                          same, 2 off (every step on one dependent chain); the
+                          results are equal */
     int32_t wait_ms;   /* longest wall-clock time one wait inside a kernel (a
                           grid barrier, or a destination waiting for its source's
                           transfer) may take before the run is abandoned with
@@ -246,12 +248,12 @@ typedef struct {
                           grid-barrier kernel always packs 64; the results do
                           not depend on it. */
     int32_t group;     /* how many nodes after the wavefront-wide ones get a
-                          group of 8 lanes each (8 nodes a wavefront), on
-                          which the lattice walk covers 3 steps per pass: 0
-                          none (the autotuner may choose some), -1 all, else
-                          that many.  Only where the lattice walk applies (see
-                          lattice) and not in the grid-barrier kernel; the
-                          results do not depend on it. */
+                          group of 8 lanes each (8 nodes a wavefront), which
+                          makes 8 steps per pass: 0 none (the autotuner may
+                          choose some), -1 all, else that many.  Only where
+                          windows of steps apply (see lattice) and not in the
+                          grid-barrier kernel; the results do not depend on
+                          it. */
     int32_t lane_queue;/* models without external transfers: 1 every node on one
                           lane that advances its node day by day on its own and,
                           when the node is done, takes the next node of its

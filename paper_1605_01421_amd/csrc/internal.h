@@ -166,9 +166,9 @@ struct KParams {
     int32_t pipeline;            // 1: overlap the next step's random numbers with this step
     int32_t nbig;                // the first nbig nodes each get a whole wavefront
     int32_t ngrp;                // the next ngrp nodes get a group of lanes each (the
-    int32_t ngw;                 //   lattice walk on a group), ngw wavefronts of them
+    int32_t ngw;                 //   windows of steps on a group), ngw wavefronts of them
     int32_t nmajor;              // nbig + ngrp: nodes whose records are node-major
-    int32_t lattice;             // wide nodes walk a lattice of reachable states
+    int32_t lattice;             // nodes on 64 or GROUP_LANES lanes make a window of steps at once
     uint64_t wait_ticks;         // wall-clock ticks one wait may last before abort
     const RunParams* rp;         // seed and stream base of the current run (device)
     int32_t lane_queue;          // free-running, one lane per node, each lane advancing its

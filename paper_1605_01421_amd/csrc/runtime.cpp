@@ -358,7 +358,7 @@ int configure(siminf_model* m, Group& g, int block, int nbig, int pipeline, int 
     const int cus = device_cus(m);
     if (cus <= 0) return SIMINF_E_DEVICE;
     nbig = std::max(0, std::min(nbig, n));
-    // nodes on a group of lanes: only where the lattice walk applies
+    // nodes on a group of lanes: only where the windows apply
     const int per_grp = WAVE / GROUP_LANES;
     ngrp = p.lattice ? std::max(0, std::min(ngrp, n - nbig)) : 0;
     // pack 0 (auto): 64 nodes to a wavefront, unless that leaves CUs without a
@@ -950,10 +950,12 @@ int create_impl(const siminf_spec* specs, int nspecs, const int32_t* reps, const
                 if (sp.G[k + (size_t)j * g.shape.nt]) mask |= 1u << k;
             p.Gmask[j] = mask;
         }
-        p.lattice = !is_generated(g.model) && m->opt.lattice != 2 && g.shape.nt == 2 && p.Gmask[0] == 3u &&
-                            p.Gmask[1] == 3u
-                        ? 1
-                        : 0;
+        // the speculative window on the lanes of a node: G marks both rates
+        // after either transition, and the entries of S fit its 24-bit products
+        // of up to 64 steps
+        bool small_S = !is_generated(g.model);
+        for (int k = 0; small_S && k < nc * g.shape.nt; ++k) small_S = p.S[k] >= -(1 << 20) && p.S[k] <= (1 << 20);
+        p.lattice = small_S && m->opt.lattice != 2 && g.shape.nt == 2 && p.Gmask[0] == 3u && p.Gmask[1] == 3u ? 1 : 0;
         int32_t *d_u0, *d_nrun, *d_nidx, *d_e1off, *d_e2step, *d_e2lvl, *d_e2noff;
         double *d_v0, *d_ld;
         int64_t* d_nord;
@@ -1505,7 +1507,7 @@ int siminf_autotune(siminf_model* m, uint64_t seed, int32_t repeats, void* hip_s
                 if (div != second.wide_div) consider({second.block, div, second.pipeline, second.pack, -1, 0});
         }
         // then the heaviest nodes after the wide ones on groups of lanes (the
-        // lattice walk on GROUP_LANES lanes): an eighth, a quarter, half or
+        // a window of steps on GROUP_LANES lanes): an eighth, a quarter, half or
         // all of them, with the packing chosen so far or 16 or 8 nodes per
         // one-lane wavefront (groups take more wavefronts, and a launch whose
         // wavefronts cannot all be resident drops them)

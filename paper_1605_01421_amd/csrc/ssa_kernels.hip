@@ -313,378 +313,251 @@ __device__ __forceinline__ int ssa_wide(const KParams& p, Node<M>& s, double t, 
     }
 }
 
-// Steps per window of the lattice walk, the lanes its points occupy, and
-// the draws of one block (a whole number of windows).
-constexpr int LAT_W = 10;
-constexpr int LAT_POINTS = LAT_W * (LAT_W + 1) / 2;
-constexpr int LAT_BLOCK = 60;
-static_assert(LAT_POINTS <= WAVE && LAT_BLOCK <= WAVE && LAT_BLOCK % LAT_W == 0, "the lattice must fit one wavefront");
-
-// The points of a window's path: pl[k + 1] = pl[k] + k + 1 + (bit pl[k] of
-// mask), each on the scalar unit as a bit test that sets SCC and an add with
-// carry of the constant k + 1 (arithmetic only; SCC is set and used inside
-// the block).
-template <int K>
-__device__ __forceinline__ void lattice_path(unsigned long long mask, int (&pl)[LAT_W + 1]) {
-    if constexpr (K < LAT_W) {
-        int r;
-        asm("s_bitcmp1_b64 %1, %2\n\ts_addc_u32 %0, %2, %3" : "=s"(r) : "s"(mask), "s"(pl[K]), "n"(K + 1) : "scc");
-        pl[K + 1] = r;
-        lattice_path<K + 1>(mask, pl);
-    }
-}
-
-// What one pass of the lattice walk gives a lane: the values of the step
-// taken from its point, and the check of its state (1 a negative
-// compartment, 2 a bad rate, 4 lambda <= 0: the node stops for the day).  A
-// state that fails its checks is never left by a step, so its tau is +inf;
-// a state that passes has lambda > 0 and a finite tau >= 0.  `first` has bit
-// L set when the step from point L is of the first kind.
-struct LatticePass {
-    double tau, lam;
-    int chk;
-    unsigned long long first;
+// ---------------------------------------------------------------------------
+// the speculative window: G lanes carry one node, G steps a pass
+// ---------------------------------------------------------------------------
+// The choices of a group's G lanes, one bit a lane (bit j: the step of lane j
+// is of the first kind), the same in every lane of the group.
+template <int G>
+struct LaneBits {
+    using type = uint32_t;
+};
+template <>
+struct LaneBits<WAVE> {
+    using type = unsigned long long;
 };
 
-// Lane (lk, la) evaluates the state lk steps ahead of u with la transitions
-// of the first kind, with the variates e, r2 of step lk.
-template <class M>
-__device__ __forceinline__ LatticePass lattice_pass(const Node<M>& s, const int32_t (&u)[M::NC], int lk, int la,
-                                                    const int32_t (&S0)[M::NC], const int32_t (&S1)[M::NC],
-                                                    double e, double r2) {
-    int32_t uc[M::NC];
-    bool neg = false;
-#pragma unroll
-    for (int c = 0; c < M::NC; ++c) {
-        uc[c] = u[c] + la * S0[c] + (lk - la) * S1[c];
-        neg |= uc[c] < 0;
-    }
-    const double c0 = M::template rate<0>(uc, s.v, s.ld, s.gd);
-    const double c1 = M::template rate<1>(uc, s.v, s.ld, s.gd);
-    LatticePass r;
-    double lam = 0.0;
-    lam = lam + c0;
-    lam = lam + c1;
-    r.lam = lam;
-    const double x = lam * r2;
-    const int n = (c0 > 0.0 && x <= c0) ? 0 : (c1 > 0.0 ? 1 : 0);
-    r.chk = neg ? 1 : !(rate_ok(c0) && rate_ok(c1)) ? 2 : !(lam > 0.0) ? 4 : 0;
-    r.tau = r.chk ? __builtin_inf() : e / lam;
-    r.first = __ballot(n == 0);
-    return r;
+template <int G>
+__device__ __forceinline__ typename LaneBits<G>::type group_bits(bool b, int gb) {
+    const unsigned long long all = __ballot(b);
+    if constexpr (G == WAVE)
+        return all;
+    else
+        return (uint32_t)(all >> gb) & (uint32_t)((1ull << G) - 1ull);
+}
+// index of the first set bit, G if there is none
+template <int G>
+__device__ __forceinline__ int first_bit(typename LaneBits<G>::type x) {
+    if constexpr (G == WAVE)
+        return x ? __builtin_ctzll(x) : G;
+    else
+        return x ? __builtin_ctz(x) : G;
+}
+// set bits below bit j (0 <= j <= G)
+template <int G>
+__device__ __forceinline__ int bits_below(typename LaneBits<G>::type x, int j) {
+    if constexpr (G == WAVE)
+        return __builtin_popcountll(j >= WAVE ? x : x & ((1ull << j) - 1ull));
+    else
+        return __builtin_popcount(x & (uint32_t)((1ull << j) - 1ull));
+}
+// whether b holds in some group of the wavefront (b is the same in every lane
+// of a group; with G = 64 it is uniform)
+template <int G>
+__device__ __forceinline__ bool some_group(bool b) {
+    if constexpr (G == WAVE)
+        return b;
+    else
+        return __any(b);
 }
 
-// The same SSA for one heavy node on a whole wavefront, with the serial chain
-// cut to a few instructions per step.  With two transitions, the state k
-// steps ahead is u + a S[:,0] + (k - a) S[:,1] for some 0 <= a <= k.  One
-// wavefront-wide pass evaluates, for every lattice point (k, a) of the next
-// LAT_W steps at once, all that a step computes from its state: the checks
-// of the state, the rates, lambda, tau = E_k / lambda (E_k is the
-// exponential variate of step k), and the inversion choice with r2_k.  The
-// walk then follows the realised path: per step it reads tau from the lane
-// of the current point and advances t by one addition, and it stops at the
-// day boundary.  The path, and so the window's end state, is known before
-// the time additions: the next window's pass is computed alongside them and
-// used if the window does not stop.  Every value comes from the same
-// operations in the same order as in ssa_to_boundary, so the result is
-// bit-identical.  Valid when G marks both rates after either transition: a
-// full recomputation then equals the incremental one.
-template <class M>
-__device__ __forceinline__ int ssa_lattice(const KParams& p, Node<M>& s, double t, double T, uint32_t day_word,
-                                           uint32_t node, uint32_t stream, unsigned long long& transitions,
-                                           unsigned long long& draws) {
-    {
-        // the day's first state, checked as the walk's first pass would (a
-        // node whose rates are all zero costs no draw)
-        bool neg = false;
-#pragma unroll
-        for (int c = 0; c < M::NC; ++c) neg |= s.u[c] < 0;
-        if (neg) return E_NEG_STATE;
-        const double w0 = M::template rate<0>(s.u, s.v, s.ld, s.gd);
-        const double w1 = M::template rate<1>(s.u, s.v, s.ld, s.gd);
-        if (!rate_ok(w0) || !rate_ok(w1)) return E_BAD_RATE;
-        double lam = 0.0;
-        lam = lam + w0;
-        lam = lam + w1;
-        if (!(lam > 0.0)) return 0;
-    }
-    const int lane = threadIdx.x & (WAVE - 1);
-    int lk = 0;
-    while ((lk + 1) * (lk + 2) / 2 <= lane) ++lk;
-    const int la = lane - lk * (lk + 1) / 2;
-    const uint32_t k0 = (uint32_t)p.seed, k1 = (uint32_t)(p.seed >> 32);
-    const uint32_t tag = stream & 0xFFFFFFu;
-    int32_t S0[M::NC], S1[M::NC], Sw[M::NC], Sd[M::NC];
-#pragma unroll
-    for (int c = 0; c < M::NC; ++c) {
-        S0[c] = p.S[c];
-        S1[c] = p.S[c + M::NC];
-        Sw[c] = LAT_W * S1[c];  // a full window with a first-kind steps moves
-        Sd[c] = S0[c] - S1[c];  // the state by Sw + a Sd
-    }
-    uint32_t nd = 0, ntr = 0;  // draws and transitions, wave-uniform
-    int rc = 0;
-    // Draws come in blocks of LAT_BLOCK (lane j of the block at mb draws step
-    // mb + j); the window at draw g (a multiple of LAT_W) reads the lanes
-    // g - mb + lk of its block.
-    const int lsrc = lk < LAT_W ? lk : 0;
-    uint32_t mb = 0;
-    StepRandoms mine = step_randoms(k0, k1, (uint32_t)lane, day_word, node, tag);
-    auto ensure_block = [&](uint32_t g) {
-        if (g - mb >= (uint32_t)LAT_BLOCK) {
-            mb = g;
-            mine = step_randoms(k0, k1, g + (uint32_t)lane, day_word, node, tag);
-        }
-    };
-    LatticePass P = lattice_pass<M>(s, s.u, lk, la, S0, S1, __shfl(mine.e, lsrc, WAVE), __shfl(mine.r2, lsrc, WAVE));
-#pragma unroll 1
-    for (uint32_t g = 0;; g += LAT_W) {
-        const double t_in = t;
-        const bool near_limit = g <= STEP_LIMIT && STEP_LIMIT - g < (uint32_t)LAT_W;
-        // Fast path, taken by every window but the day's last: the path in
-        // scalar registers, tau read from the lane of each point in turn.
-        // The times only grow (every tau is >= 0), so a window that ends
-        // before T neither crosses the boundary nor meets a failing state.
-        // A window that starts less than twice its expected length before T
-        // (or in a state without a positive rate) goes to the slow path at
-        // once: it most likely stops there.
-        if (!near_limit && (T - t) * read_lane(P.lam, 0) > 2.0 * LAT_W) {
-            ensure_block(g + LAT_W);
-            const int src = (int)(g + LAT_W - mb) + lsrc;
-            const double en = __shfl(mine.e, src, WAVE);
-            const double r2n = __shfl(mine.r2, src, WAVE);
-            // point of step k; the path's last point is LAT_POINTS + a (every
-            // step k adds k + 1, and 1 more if of the first kind)
-            int pl[LAT_W + 1];
-            pl[0] = 0;
-            lattice_path<0>(P.first, pl);
-            const int a = pl[LAT_W] - LAT_POINTS;
-            int32_t un[M::NC];
-#pragma unroll
-            for (int c = 0; c < M::NC; ++c) un[c] = s.u[c] + Sw[c] + a * Sd[c];
-            // the next window's pass, from the state this one ends in
-            const LatticePass Pn = lattice_pass<M>(s, un, lk, la, S0, S1, en, r2n);
-            double tv[LAT_W];
-#pragma unroll
-            for (int k = 0; k < LAT_W; ++k) tv[k] = read_lane(P.tau, pl[k]);
-#pragma unroll
-            for (int k = 0; k < LAT_W; ++k) t = t + tv[k];
-            // the next pass is needed only if the window goes through; this
-            // empty statement makes it be computed here, beside the time
-            // additions, rather than after the test (no instruction)
-            asm volatile("" ::"v"(Pn.tau), "v"(Pn.lam), "v"(Pn.chk));
-            if (t < T) {
-#pragma unroll
-                for (int c = 0; c < M::NC; ++c) s.u[c] = un[c];
-                nd += (uint32_t)LAT_W;
-                ntr += (uint32_t)LAT_W;
-                P = Pn;
-                continue;
-            }
-            t = t_in;
-        }
-        // Slow path (the window that stops).  The window's first state (the
-        // day's starting state or the one the previous window ended in) is
-        // checked before its first draw.
-        const int c00 = __builtin_amdgcn_readfirstlane(P.chk);
-        if (c00) {
-            rc = (c00 & 1) ? E_NEG_STATE : (c00 & 2) ? E_BAD_RATE : 0;
-            break;
-        }
-        // Lane k records the point and a of step k, and the point the step
-        // leads to.
-        int pidx = 0, pa = 0, pnext = 0;
-        int L = 0, a = 0;
-#pragma unroll
-        for (int k = 0; k < LAT_W; ++k) {
-            pidx = lane == k ? L : pidx;
-            pa = lane == k ? a : pa;
-            const int d = (int)((P.first >> L) & 1ull);
-            a += d;
-            L += k + 1 + d;
-            pnext = lane == k ? L : pnext;
-        }
-        const double tp = __shfl(P.tau, pidx, WAVE);
-        const int chk_next = __shfl(P.chk, pnext < WAVE ? pnext : 0, WAVE);
-        // the time chain: lane k keeps the time before step k; t + tau of
-        // each step is one addition, in order
-        double tl = t;
-#pragma unroll
-        for (int k = 0; k < LAT_W; ++k) {
-            tl = lane == k ? t : tl;
-            t = t + read_lane(tp, k);
-        }
-        // first step whose draw would cross the boundary, first step whose
-        // transition leads to a state that fails its checks (the last step's
-        // successor is checked by the next window), and the step whose draw
-        // would exceed the step limit.  A failing state's tau of +inf can add
-        // a crossing one step after the failure, which the failure precedes.
-        const unsigned long long cross = __ballot(lane < LAT_W && tl + tp >= T);
-        const unsigned long long fail = __ballot(lane + 1 < LAT_W && chk_next != 0);
-        const int kc = cross ? __builtin_ctzll(cross) : WAVE;
-        const int kf = fail ? __builtin_ctzll(fail) : WAVE;
-        const int kl = near_limit ? (int)(STEP_LIMIT - g) : WAVE;
-        int kend, aend;
-        bool done = true;
-        if (kl < LAT_W && kl <= kc && kl <= kf) {
-            // the draw with index STEP_LIMIT: the implementation limit
-            kend = kl;
-            aend = __builtin_amdgcn_readlane(pa, kl);
-            nd += (uint32_t)kl;
-            ntr += (uint32_t)kl;
-            rc = E_STEP_LIMIT;
-        } else if (kc <= kf && kc < LAT_W) {
-            // stops at the boundary before the transition of step kc
-            kend = kc;
-            aend = __builtin_amdgcn_readlane(pa, kc);
-            nd += (uint32_t)kc + 1u;
-            ntr += (uint32_t)kc;
-        } else if (kf < LAT_W) {
-            // the transition of step kf leads to a failing state
-            kend = kf + 1;
-            aend = __builtin_amdgcn_readlane(pa, kf + 1);
-            const int code = __builtin_amdgcn_readlane(chk_next, kf);
-            rc = (code & 1) ? E_NEG_STATE : (code & 2) ? E_BAD_RATE : 0;
-            nd += (uint32_t)kf + 1u;
-            ntr += (uint32_t)kf + 1u;
-        } else {
-            kend = LAT_W;
-            aend = a;
-            nd += (uint32_t)LAT_W;
-            ntr += (uint32_t)LAT_W;
-            done = false;
-        }
-#pragma unroll
-        for (int c = 0; c < M::NC; ++c) s.u[c] += aend * S0[c] + (kend - aend) * S1[c];
-        if (done) break;
-        // the window ran through: the next one's pass
-        ensure_block(g + LAT_W);
-        const int src = (int)(g + LAT_W - mb) + lsrc;
-        P = lattice_pass<M>(s, s.u, lk, la, S0, S1, __shfl(mine.e, src, WAVE), __shfl(mine.r2, src, WAVE));
-    }
-    if (lane == 0) {
-        draws += nd;
-        transitions += ntr;
-    }
-    return rc;
+// x moved up within the rows of 16 lanes (or broadcast between rows) by the
+// data-parallel primitive CTRL; lanes without a source get +0.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_up(double x) {
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+// Inclusive sum over the lanes of a group (gl: the lane's place in it).
+template <int G>
+__device__ __forceinline__ double group_scan(double x, int gl) {
+    static_assert(G == 8 || G == 16 || G == 32 || G == 64, "a group is 8 lanes or whole rows of 16");
+    double y = dpp_up<0x111, 0xf>(x);  // row_shr:1
+    x = x + (G < 16 && gl < 1 ? 0.0 : y);
+    y = dpp_up<0x112, 0xf>(x);  // row_shr:2
+    x = x + (G < 16 && gl < 2 ? 0.0 : y);
+    y = dpp_up<0x114, 0xf>(x);  // row_shr:4
+    x = x + (G < 16 && gl < 4 ? 0.0 : y);
+    if constexpr (G >= 16) x = x + dpp_up<0x118, 0xf>(x);  // row_shr:8
+    if constexpr (G >= 32) x = x + dpp_up<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+    if constexpr (G >= 64) x = x + dpp_up<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+// The value of lane j of the group (gb: the group's first lane).
+template <int G>
+__device__ __forceinline__ double group_read(double x, int gb, int j) {
+    if constexpr (G == WAVE)
+        return read_lane(x, j);
+    else
+        return __shfl(x, gb + j, WAVE);
 }
 
-// The lattice walk for a node carried by GRP_LANES lanes (a group; a
-// wavefront holds WAVE / GRP_LANES of them, each on its own node).  Lane
-// (lk, la) of a group evaluates the state lk steps ahead with la transitions
-// of the first kind, for the next GRP_W steps (GRP_POINTS lanes; the other
-// lanes of the group idle in the pass).  The group's lanes draw GRP_BLOCK
-// steps' random numbers at once (lane j draws step base + j).  Eight lanes
-// and three steps a pass measured faster than sixteen and five, or four and
-// two, on SIR with events over 10,000 nodes.  The path is
-// read from the group's bits of one ballot; tau and the check of each point
-// on it are then gathered and the steps are walked in order, each lane of
-// the group doing the same (group-uniform) work, with exactly the checks and
-// counts of ssa_to_boundary.  Must be called by every lane of the wavefront
-// (it shuffles and ballots); `live` marks the groups whose node steps.
-constexpr int GRP_LANES = GROUP_LANES;
-constexpr int GRP_W = 3;
-constexpr int GRP_POINTS = GRP_W * (GRP_W + 1) / 2;
-constexpr int GRP_BLOCK = 6;
-static_assert(GRP_POINTS < GRP_LANES && GRP_BLOCK <= GRP_LANES && GRP_BLOCK % GRP_W == 0 && WAVE % GRP_LANES == 0,
-              "a group's lattice must fit its lanes");
-
-template <class M>
-__device__ __forceinline__ int ssa_group(const KParams& p, Node<M>& s, bool live, double t, double T,
-                                         uint32_t day_word, uint32_t node, uint32_t stream,
-                                         unsigned long long& transitions, unsigned long long& draws) {
+// The same SSA for a node carried by G lanes: lane j of the group makes step
+// g + j of the day, all G steps of a window at once.  Lane j draws the random
+// numbers of its step, which do not depend on the state.  Its state does: with
+// two transitions it is u + a S[:,0] + (j - a) S[:,1], a the number of the
+// window's first j steps that are of the first kind.  The choices are guessed
+// from the window's starting rates, every lane evaluates its step from the
+// state that the guess gives it, and the choices that come out are compared
+// with the guess: up to the first lane where they differ (and in that lane)
+// every state was the true one, so those choices are final.  They replace the
+// guess, and the evaluation is repeated until no difference is left below the
+// steps that the day still has.  The rates change little over a window, so
+// this takes two evaluations most of the time; each one settles at least one
+// more step, so it ends.
+//
+// The times t <- t + tau are sums in the order of the steps, each rounded.  For
+// t in [1, ..) the day lies within one binade [2^e, 2^(e+1)] and every time is
+// a multiple of its unit u = 2^(e-52), so rounding t + tau to that unit moves
+// t by d = round(tau / u) u, the same for every t there unless tau / u is
+// halfway between two whole numbers (then the parity of t / u decides).
+// d = (t0 + tau) - t0 is that multiple, all partial sums of d are exact, and
+// the G times are one prefix sum; a step that would pass the binade's end
+// passes T as well.  A halfway case (tau - d is exactly +-u/2) or a day that
+// starts below 1 takes the additions one by one.
+//
+// Every value comes from the same operations as in ssa_to_boundary, with its
+// checks in the same order (a failing state's tau is +inf), so the results are
+// bit-identical.  Valid when G marks both rates after either transition (a full
+// recomputation then equals the incremental one) and the entries of S are
+// small (24-bit products).  Must be called by every lane of the wavefront;
+// `live` marks the groups whose node steps.
+//
+// What bounds it: a node's steps are one dependent chain of Philox block,
+// logarithm, division, rates and choice; here about 280 instructions make G
+// steps of it.  A lattice of the states reachable in 10 (64 lanes) or 3 (8
+// lanes) steps, walked step by step, was the earlier form.  One node alone on
+// the device, per draw: SISe of 200,000 at 14,000 draws a day 47.4 -> 11.6 ns,
+// SIR of 200,000 54.9 -> 13.0 ns, SIR of 5,000 at 22 draws a day 131 -> 77 ns.
+// Groups of 8 lanes and of 16 were within 8% of each other (SIR with events,
+// 10,000 nodes: 1.54 and 1.72 ms); 8 fit twice the nodes on the device.
+template <class M, int G>
+__device__ __forceinline__ int ssa_window(const KParams& p, Node<M>& s, bool live, double t, double T,
+                                          uint32_t day_word, uint32_t node, uint32_t stream,
+                                          unsigned long long& transitions, unsigned long long& draws) {
+    using Bits = typename LaneBits<G>::type;
     const int lane = threadIdx.x & (WAVE - 1);
-    const int gl = lane % GRP_LANES;
-    const int gb = lane - gl;  // the group's first lane
-    int lk = 0;
-    while (lk < GRP_W - 1 && (lk + 1) * (lk + 2) / 2 <= gl) ++lk;
-    const int la = gl < GRP_POINTS ? gl - lk * (lk + 1) / 2 : 0;
+    const int gl = lane % G;
+    const int gb = lane - gl;
     const uint32_t k0 = (uint32_t)p.seed, k1 = (uint32_t)(p.seed >> 32);
     const uint32_t tag = stream & 0xFFFFFFu;
-    int32_t S0[M::NC], S1[M::NC];
-#pragma unroll
-    for (int c = 0; c < M::NC; ++c) {
-        S0[c] = p.S[c];
-        S1[c] = p.S[c + M::NC];
-    }
-    uint32_t nd = 0, ntr = 0;  // group-uniform
     int rc = 0;
     bool done = !live;
-    uint32_t g = 0, mb = 0;
-    StepRandoms mine = step_randoms(k0, k1, (uint32_t)gl, day_word, node, tag);
-    while (__any(!done)) {
-        // refill the group's block when this window's draws leave it (the
-        // groups still walking all sit at the same draw g)
-        const bool refill = !done && g + GRP_W - mb > (uint32_t)GRP_BLOCK;
-        if (__any(refill)) {
-            if (refill) {
-                mb = g;
-                mine = step_randoms(k0, k1, g + (uint32_t)gl, day_word, node, tag);
+    double w0, w1, lam;
+    {
+        // the day's first state (a node without a positive rate costs no draw)
+        if constexpr (G == WAVE) {
+#pragma unroll
+            for (int c = 0; c < M::NC; ++c) s.u[c] = __builtin_amdgcn_readfirstlane(s.u[c]);
+        }
+        w0 = M::template rate<0>(s.u, s.v, s.ld, s.gd);
+        w1 = M::template rate<1>(s.u, s.v, s.ld, s.gd);
+        lam = 0.0;
+        lam = lam + w0;
+        lam = lam + w1;
+        const int code = !(rate_ok(w0) && rate_ok(w1)) ? E_BAD_RATE : 0;
+        const bool still = code != 0 || !(lam > 0.0);
+        if constexpr (G == WAVE) {
+            if (__builtin_amdgcn_readfirstlane(still ? 1 : 0)) return __builtin_amdgcn_readfirstlane(code);
+        } else {
+            rc = !done && still ? code : 0;
+            done = done || still;
+            if (!__any(!done)) return rc;
+        }
+    }
+    int32_t Sw[M::NC], Sd[M::NC];  // the state of lane gl is u + Sw + a Sd
+#pragma unroll
+    for (int c = 0; c < M::NC; ++c) {
+        Sw[c] = __mul24(gl, p.S[c + M::NC]);
+        Sd[c] = p.S[c] - p.S[c + M::NC];
+    }
+    uint32_t nd = 0, ntr = 0;  // the same in every lane of the group
+#pragma unroll 1
+    for (uint32_t g = 0; some_group<G>(!done); g += (uint32_t)G) {
+        const StepRandoms r = step_randoms(k0, k1, g + (uint32_t)gl, day_word, node, tag);
+        // the steps that the day most likely still has: the first ones to settle
+        const float mu = (float)((T - t) * lam);
+        int lim = mu < (float)G ? min(G, (int)(mu * 1.25f) + 4) : G;
+        Bits bits = group_bits<G>(w0 > 0.0 && lam * r.r2 <= w0, gb);
+        const int kl = g <= STEP_LIMIT && STEP_LIMIT - g < (uint32_t)G ? (int)(STEP_LIMIT - g) : G;
+        bool open = !done;  // the group's window is not settled yet
+        double c0, c1, cl;
+        while (some_group<G>(open)) {
+            // every lane's step from the state that the guess gives it
+            const int a = bits_below<G>(bits, gl);
+            int32_t uc[M::NC];
+            bool neg = false;
+#pragma unroll
+            for (int c = 0; c < M::NC; ++c) {
+                uc[c] = s.u[c] + Sw[c] + __mul24(a, Sd[c]);
+                neg |= uc[c] < 0;
             }
-        }
-        const int src = gb + (done ? 0 : (int)(g - mb)) + lk;
-        const double e = __shfl(mine.e, src, WAVE);
-        const double r2 = __shfl(mine.r2, src, WAVE);
-        // the pass (as in lattice_pass, per group)
-        int32_t uc[M::NC];
-        bool neg = false;
+            c0 = M::template rate<0>(uc, s.v, s.ld, s.gd);
+            c1 = M::template rate<1>(uc, s.v, s.ld, s.gd);
+            cl = 0.0;
+            cl = cl + c0;
+            cl = cl + c1;
+            const double x = cl * r.r2;
+            const int n = (c0 > 0.0 && x <= c0) ? 0 : (c1 > 0.0 ? 1 : 0);
+            const int chk = neg ? 1 : !(rate_ok(c0) && rate_ok(c1)) ? 2 : !(cl > 0.0) ? 4 : 0;
+            const Bits got = group_bits<G>(n == 0, gb);
+            const int fm = first_bit<G>(got ^ bits);  // states and choices of lanes < fm, the state of lane fm: final
+            const int fc = first_bit<G>(group_bits<G>(chk != 0, gb));
+            const bool settled = fm >= min(lim, fc);
+            if (some_group<G>(open && !settled)) {
+                if (open && !settled) bits = got;
+                continue;
+            }
+            // the times after each step
+            const double tau = chk ? __builtin_inf() : r.e / cl;
+            const double d = (t + tau) - t;
+            const double half = __longlong_as_double((__double_as_longlong(t) & 0x7ff0000000000000ll) - (53ll << 52));
+            double tn = t + group_scan<G>(d, gl);
+            if (__any(open && (__builtin_fabs(tau - d) == half || !(t >= 1.0)))) {
+                double tl = t;
+#pragma unroll 1
+                for (int k = 0; k < G; ++k) {
+                    tl = tl + group_read<G>(tau, gb, k);
+                    tn = gl == k ? tl : tn;
+                }
+            }
+            const int kc = first_bit<G>(group_bits<G>(tn >= T, gb));
+            // the first lane whose state fails its checks (before its draw),
+            // whose draw has the index STEP_LIMIT, or whose step crosses T
+            const int ks = min(min(fc, kl), kc);
+            const bool stop = ks < G && ks <= fm;
+            const bool full = !stop && fm >= G;
+            if (open && !stop && !full) {
+                // the day goes on past the settled steps: settle the others
+                lim = G;
+                bits = got;
+            }
+            if (open && (stop || full)) {
+                open = false;
+                const int to = stop ? ks : G;  // transitions made in the window
+                const int at = bits_below<G>(bits, to);
 #pragma unroll
-        for (int c = 0; c < M::NC; ++c) {
-            uc[c] = s.u[c] + la * S0[c] + (lk - la) * S1[c];
-            neg |= uc[c] < 0;
-        }
-        const double c0 = M::template rate<0>(uc, s.v, s.ld, s.gd);
-        const double c1 = M::template rate<1>(uc, s.v, s.ld, s.gd);
-        double lam = 0.0;
-        lam = lam + c0;
-        lam = lam + c1;
-        const double x = lam * r2;
-        const int n = (c0 > 0.0 && x <= c0) ? 0 : (c1 > 0.0 ? 1 : 0);
-        const int chk = neg ? 1 : !(rate_ok(c0) && rate_ok(c1)) ? 2 : !(lam > 0.0) ? 4 : 0;
-        const double tau = chk ? 0.0 : e / lam;
-        const unsigned long long first = __ballot(n == 0);
-        const uint32_t mask = (uint32_t)(first >> gb) & ((1u << GRP_POINTS) - 1u);
-        // the path: point of step k, and whether that step is of the first kind
-        int pl[GRP_W], pd[GRP_W];
-        int L = 0;
-#pragma unroll
-        for (int k = 0; k < GRP_W; ++k) {
-            pl[k] = L;
-            pd[k] = (int)((mask >> L) & 1u);
-            L += k + 1 + pd[k];
-        }
-        double tk[GRP_W];
-        int ck[GRP_W];
-#pragma unroll
-        for (int k = 0; k < GRP_W; ++k) {
-            tk[k] = __shfl(tau, gb + pl[k], WAVE);
-            ck[k] = __shfl(chk, gb + pl[k], WAVE);
-        }
-        // the steps in order: the state's checks, the step limit, the draw,
-        // the day boundary, the transition
-        // (as selects: the groups of a wavefront stop at different steps)
-        int kapp = 0, aapp = 0;  // transitions applied in this window, of the first kind
-        bool stop = done;
-#pragma unroll
-        for (int k = 0; k < GRP_W; ++k) {
-            const bool bad = !stop && ck[k] != 0;
-            const bool lim = !stop && !bad && g + (uint32_t)k == STEP_LIMIT;
-            const bool draw = !stop && !bad && !lim;
-            const double tn = t + tk[k];
-            const bool go = draw && !(tn >= T);
-            rc = bad ? ((ck[k] & 1) ? E_NEG_STATE : (ck[k] & 2) ? E_BAD_RATE : 0) : lim ? E_STEP_LIMIT : rc;
-            nd += draw ? 1u : 0u;
-            t = go ? tn : t;
-            kapp += go ? 1 : 0;
-            aapp += go ? pd[k] : 0;
-            stop = stop || !go;
-        }
-        ntr += (uint32_t)kapp;
-        if (!done) {
-#pragma unroll
-            for (int c = 0; c < M::NC; ++c) s.u[c] += aapp * S0[c] + (kapp - aapp) * S1[c];
-            done = stop;
-            g += (uint32_t)GRP_W;
+                for (int c = 0; c < M::NC; ++c) s.u[c] = s.u[c] + __mul24(to, p.S[c + M::NC]) + __mul24(at, Sd[c]);
+                ntr += (uint32_t)to;
+                nd += (uint32_t)to;
+                if (stop) {
+                    done = true;
+                    if (ks == fc) {
+                        const int code = G == WAVE ? __builtin_amdgcn_readlane(chk, fc) : __shfl(chk, gb + fc, WAVE);
+                        rc = (code & 1) ? E_NEG_STATE : (code & 2) ? E_BAD_RATE : 0;
+                    } else if (ks == kl) {
+                        rc = E_STEP_LIMIT;
+                    } else {
+                        nd += 1u;  // the draw that crosses the boundary
+                    }
+                } else {
+                    t = group_read<G>(tn, gb, G - 1);
+                    w0 = group_read<G>(c0, gb, G - 1);  // close enough to the next window's
+                    lam = group_read<G>(cl, gb, G - 1); // starting rates for a guess
+                }
+            }
         }
     }
     if (gl == 0) {
@@ -924,7 +797,7 @@ __device__ __forceinline__ void group_day(const KParams& p, Node<M>& s, bool liv
     const double T = (double)day;
     const double t0 = b == 0 ? p.t0 : T - 1.0;
     int rc = 0;
-    if constexpr (!M::GENERATED) rc = ssa_group<M>(p, s, live, t0, T, (uint32_t)(int32_t)day, node, stream, t.tr, t.dr);
+    if constexpr (!M::GENERATED) rc = ssa_window<M, GROUP_LANES>(p, s, live, t0, T, (uint32_t)(int32_t)day, node, stream, t.tr, t.dr);
     if (!live) return;
     if (rc) {
         raise_error(p.ctrl, b, PH_SSA, ord, rc);
@@ -1065,7 +938,7 @@ __device__ __forceinline__ int ssa_aem(const KParams& p, Node<M>& s, AemState<M,
 }
 
 // SSA to day boundary b, then the node's E1 events with time <= T.  With
-// wide, the whole wavefront carries the node (the lattice walk, or the plain
+// wide, the whole wavefront carries the node (windows of 64 steps, or the plain
 // chain when G does not mark both rates); event tallies are then kept by
 // lane 0 only.  With AEM, the all events method on one lane.
 template <class M, bool PIPE, bool AEM = false>
@@ -1082,7 +955,7 @@ __device__ __forceinline__ void ssa_and_e1(const KParams& p, Node<M>& s, int b, 
         rc = ssa_to_boundary<M, PIPE>(p, s, t0, T, dw, node, stream, t.tr, t.dr);  // never wide
     else
         rc = !wide       ? ssa_to_boundary<M, PIPE>(p, s, t0, T, dw, node, stream, t.tr, t.dr)
-             : p.lattice ? ssa_lattice<M>(p, s, t0, T, dw, node, stream, t.tr, t.dr)
+             : p.lattice ? ssa_window<M, WAVE>(p, s, true, t0, T, dw, node, stream, t.tr, t.dr)
                          : ssa_wide<M>(p, s, t0, T, dw, node, stream, t.tr, t.dr);
     if (rc) {
         raise_error(p.ctrl, b, PH_SSA, ord, rc);
@@ -1112,15 +985,15 @@ __global__ void __launch_bounds__(256) free_kernel(KParams pa) {
         chunk = __shfl(chunk, 0, WAVE);
         if (chunk >= (unsigned)p.nchunks) break;
         // chunks [0, nbig): one heavy node per wavefront; then ngw chunks of
-        // WAVE / GRP_LANES nodes with GRP_LANES lanes each; then pack nodes per chunk
+        // WAVE / GROUP_LANES nodes with GROUP_LANES lanes each; then pack nodes per chunk
         const int c = (int)chunk;
         const bool wide = c < p.nbig;
         const bool grp = GRP && !wide && c < p.nbig + p.ngw;
         const int k = wide  ? c
-                      : grp ? p.nbig + (c - p.nbig) * (WAVE / GRP_LANES) + lane / GRP_LANES
+                      : grp ? p.nbig + (c - p.nbig) * (WAVE / GROUP_LANES) + lane / GROUP_LANES
                             : p.nbig + p.ngrp + (c - p.nbig - p.ngw) * p.pack + lane;
         const bool active = (wide || (grp ? k < p.nbig + p.ngrp : lane < p.pack)) && k < p.n;
-        const bool owner = active && (wide ? lane == 0 : grp ? lane % GRP_LANES == 0 : true);  // writes records
+        const bool owner = active && (wide ? lane == 0 : grp ? lane % GROUP_LANES == 0 : true);  // writes records
         Node<M> s{};
         int run = 0, cur = 0, cend = 0;
         uint32_t node = 0, stream = 0;
@@ -1616,14 +1489,14 @@ __global__ void __launch_bounds__(256) flow_kernel(KParams pa) {
                    (int)(threadIdx.x / WAVE);
     // waves [0, nbig): one heavy node per wavefront
     const bool wide = gw < p.nbig;
-    // then ngw waves of WAVE / GRP_LANES nodes with GRP_LANES lanes each
+    // then ngw waves of WAVE / GROUP_LANES nodes with GROUP_LANES lanes each
     const bool grp = GRP && !wide && gw < p.nbig + p.ngw;
     // then pack nodes per wave, one lane each
     const int k = wide  ? gw
-                  : grp ? p.nbig + (gw - p.nbig) * (WAVE / GRP_LANES) + lane / GRP_LANES
+                  : grp ? p.nbig + (gw - p.nbig) * (WAVE / GROUP_LANES) + lane / GROUP_LANES
                         : p.nbig + p.ngrp + (gw - p.nbig - p.ngw) * p.pack + lane;
     const bool active = (wide || (grp ? k < p.nbig + p.ngrp : lane < p.pack)) && k < p.n;
-    const bool owner = active && (wide ? lane == 0 : grp ? lane % GRP_LANES == 0 : true);
+    const bool owner = active && (wide ? lane == 0 : grp ? lane % GROUP_LANES == 0 : true);
     Node<M> s{};
     int run = 0, cur = 0, cend = 0, tcur = 0, tend = 0;
     uint32_t node = 0, stream = 0;
