@@ -260,8 +260,11 @@ typedef struct {
                           wavefront's chunk (the throughput kernel); 2 off (the
                           lanes of a wavefront go through each day together);
                           0 auto: on when no lanes, wide, group or pack option
-                          is set and the model has at least 64 nodes per SIMD
-                          of the device.  With SIMINF_RECORD_SUMS it needs
+                          is set and the model records sums or has at least 64
+                          nodes per SIMD of the device.  The nodes that would
+                          hold one lane longest are each carried by a whole
+                          wavefront first (not with lanes = 1 or order = 1).
+                          With SIMINF_RECORD_SUMS it needs
                           2 x Ntspan x Nc x 8 bytes of LDS per wavefront (at
                           most 64 KiB per workgroup), else SIMINF_E_UNSUPPORTED
                           (auto: off).  The results do not depend on it. */

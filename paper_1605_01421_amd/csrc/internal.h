@@ -34,6 +34,7 @@ struct Ctrl {
     unsigned long long err_key;
     unsigned long long counters[4];  // transitions, node-days, events, SSA draws
     unsigned int work[MAX_GROUPS];   // work-queue cursors (free-running mode)
+    unsigned int heavy[MAX_GROUPS];  // lane queue: cursors of the heavy nodes' queues
     unsigned int bar_count;          // grid barrier arrivals
     unsigned int abort;              // set when a wait exceeded its spin limit
     unsigned int e2done;             // dataflow mode: steps whose transfers are applied
@@ -177,6 +178,8 @@ struct KParams {
     const int4* lchunks;         // [nlchunks] x = first node, y = end, z = run
     int32_t lq_batch;            // lanes that wait at their day's end before the
                                  // wavefront closes their days together
+    int32_t nheavy;              // lane queue: nodes too heavy for one lane, each carried by
+    const int32_t* heavy;        //   a whole wavefront first ([nheavy], heaviest first)
     int32_t solver;              // 0 the direct method, 1 the all events method:
     int32_t nt;                  //   transitions, and per node and channel
     double* aem_T;               //   [nt][n] the integrated rate,

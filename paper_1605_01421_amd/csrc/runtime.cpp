@@ -53,6 +53,8 @@ struct Group {
     std::vector<int32_t> node_run;  // run of each node, internal order (lane-queue chunks)
     int4* d_chunks = nullptr;       // lane-queue chunk table and its capacity
     int chunk_cap = 0;
+    int32_t* d_heavy = nullptr;     // lane queue: the heavy nodes and the table's capacity
+    int heavy_cap = 0;
     int lq_chunk = 0;               // lane queue: nodes per chunk (0 = off)
     int lq_batch = 0;               //             lanes per day-end batch
 };
@@ -257,9 +259,32 @@ int default_group(const Group& g, int nbig, int div) {
     return (g.n - nbig + div - 1) / div;
 }
 
-// Kernel and launch shape of one group.  want_mode applies to groups with
-// external transfers: 0 auto (dataflow if every node wavefront fits on the
-// device at once, else grid barrier), 1 barrier, 2 dataflow.
+// Nodes of a lane-queue group too heavy for one lane, heaviest first: each gets
+// a whole wavefront, and the lanes keep the others.  A lane makes a step in
+// about 1.4 us when the SIMDs are full, so the heaviest node that stays on a
+// lane sets a floor under the run that grows with the cut x; a wavefront makes
+// the same chain some 50 times faster but costs the device more per step, and
+// with node sizes spread like 1/x the work it takes over grows like 1/x.  The
+// sum of the two is least at a cut proportional to the mean work of a node
+// times the square root of the nodes per lane.  The factor was measured on
+// ensembles of 64 sets x 8 replicates and 20 x 4: SISe sets 94 and 24 ms at
+// 1.5 (109 and 21 at 1, 102 and 29 at 2.6, 160 and 41 at 6); SIR sets, whose
+// nodes make fewer steps a day and fill a window less, 13 and 7 ms at 5 (34
+// and 16 at 1, 14 and 10 at 2.6, 18 and 11 at 10).  With no heavy nodes the
+// SISe sets take 490 and 125 ms.
+std::vector<int32_t> heavy_nodes(const siminf_model* m, const Group& g, int64_t waves) {
+    std::vector<int32_t> out;
+    if (m->opt.order == 1 || m->opt.lanes == 1 || g.n == 0) return out;
+    const double factor = g.model == M_SIR ? 5.0 : 1.5;
+    double total = 0;
+    for (int64_t w : g.work) total += (double)w;
+    const double cut = factor * total / (double)g.n * std::sqrt((double)g.n / ((double)waves * WAVE));
+    for (int k = 0; k < g.n; ++k)
+        if ((double)g.work[k] > cut) out.push_back(k);
+    std::stable_sort(out.begin(), out.end(), [&](int32_t a, int32_t b) { return g.work[a] > g.work[b]; });
+    return out;
+}
+
 // LDS a lane-queue workgroup of wpb wavefronts needs: the day-to-record
 // table (nb + 1 ints, padded to 8 bytes), and per wavefront its recording
 // slots, the slots' global data and its counters.
@@ -298,10 +323,18 @@ int configure(siminf_model* m, Group& g, int block, int nbig, int pipeline, int 
         for (int64_t w : g.work) total += (long double)w;
         const long double budget = total / ((long double)per_cu * cus * wpb * 8.0L);
         std::vector<int4> ch;
+        const std::vector<int32_t> heavy = heavy_nodes(m, g, (int64_t)per_cu * cus * wpb);
+        std::vector<bool> is_heavy(heavy.empty() ? 0 : g.n, false);
+        for (int32_t k : heavy) is_heavy[k] = true;
         for (int k = 0; k < g.n;) {
+            // (a run's nodes are in descending order: its heavy ones come first)
+            if (!heavy.empty() && is_heavy[k]) {
+                ++k;
+                continue;
+            }
             int e = k + 1;
             long double w = (long double)g.work[k];
-            while (e < g.n && e - k < lq_chunk && g.node_run[e] == g.node_run[k] &&
+            while (e < g.n && e - k < lq_chunk && g.node_run[e] == g.node_run[k] && (heavy.empty() || !is_heavy[e]) &&
                    (e - k < WAVE || w + g.work[e] <= budget)) {
                 w += (long double)g.work[e];
                 ++e;
@@ -321,7 +354,20 @@ int configure(siminf_model* m, Group& g, int block, int nbig, int pipeline, int 
         if (!ch.empty() && hipMemcpy(g.d_chunks, ch.data(), sizeof(int4) * ch.size(), hipMemcpyHostToDevice) !=
                                hipSuccess)
             return SIMINF_E_DEVICE;
-        int blocks = std::max(1, std::min(per_cu * cus, ((int)ch.size() + wpb - 1) / wpb));
+        if (heavy.size() > (size_t)g.heavy_cap) {
+            void* grown = nullptr;
+            if (hipMalloc(&grown, sizeof(int32_t) * heavy.size()) != hipSuccess) return SIMINF_E_ALLOC;
+            m->owned.push_back(grown);
+            g.d_heavy = (int32_t*)grown;
+            g.heavy_cap = (int)heavy.size();
+        }
+        if (!heavy.empty() && hipMemcpy(g.d_heavy, heavy.data(), sizeof(int32_t) * heavy.size(),
+                                        hipMemcpyHostToDevice) != hipSuccess)
+            return SIMINF_E_DEVICE;
+        p.nheavy = (int)heavy.size();
+        p.heavy = g.d_heavy;
+        const int waves = (int)ch.size() + p.nheavy;
+        int blocks = std::max(1, std::min(per_cu * cus, (waves + wpb - 1) / wpb));
         if (m->opt.max_blocks > 0) blocks = std::min(blocks, m->opt.max_blocks);
         g.mode = MODE_FREE;
         p.mode = MODE_FREE;
@@ -1036,7 +1082,12 @@ int create_impl(const siminf_spec* specs, int nspecs, const int32_t* reps, const
             const int wpb = (m->opt.block ? m->opt.block : 256) / WAVE;
             if (m->opt.lane_queue == 1)
                 lq = chunk;
-            else if (m->opt.lane_queue == 0 && !shaped && (int64_t)n >= (int64_t)cus * 4 * WAVE &&
+            else if (m->opt.lane_queue == 0 && !shaped &&
+                     // (sums: with its heavy nodes on wavefronts the queue was
+                     // the faster kernel from 565 nodes, 2.1 against 7.6 ms, to
+                     // 84,000, 22 against 62 ms; full records of fewer nodes
+                     // are written better by the lockstep kernel)
+                     (m->record == SIMINF_RECORD_SUMS || (int64_t)n >= (int64_t)cus * 4 * WAVE) &&
                      lane_queue_lds(m, g, wpb) <= (size_t)LQ_LDS_BYTES)
                 lq = chunk;
         } else if (m->opt.lane_queue == 1) {
@@ -1403,7 +1454,7 @@ int siminf_launch_info(const siminf_model* m, int32_t out[12]) {
     out[2] = g.p.lane_queue ? 3 : g.mode;
     out[3] = g.p.pipeline;
     out[4] = m->opt.order;
-    out[5] = g.p.nbig;
+    out[5] = g.p.lane_queue ? g.p.nheavy : g.p.nbig;
     out[6] = g.p.pack;
     out[7] = g.p.ngrp;
     out[8] = g.lq_chunk;

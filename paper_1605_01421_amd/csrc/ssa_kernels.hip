@@ -1162,6 +1162,57 @@ __device__ __forceinline__ void lane_load(const KParams& p, LaneState<M>& L, int
     L.b = 0;
 }
 
+// A node too heavy for one lane, carried by the whole wavefront through all
+// its days (windows of 64 steps) before the wavefront joins the queue.  The
+// same day loop as free_kernel's wide nodes, ended early once the node can
+// no longer change (as in lane_open_day).  A run lasts at least as long as
+// its longest chain: 64 SIR and SISe sets x 8 replicates took 508 ms with
+// every node on one lane (the chain of a 50,000-animal SISe node) and take
+// 94 ms, the 4,096-run batch of 64 x 64 took 329 ms and takes 257 ms.
+template <class M>
+__device__ __forceinline__ void lane_heavy(const KParams& pa, int k, const int* rec_off, Tally& t) {
+    KParams p = pa;
+    p.seed = pa.rp->seed;
+    p.stream_base = pa.rp->stream_base;
+    const int lane = threadIdx.x & (WAVE - 1);
+    Node<M> s{};
+    int run = 0, cur = 0, cend = 0, wbase = 0;
+    uint32_t node = 0, stream = 0;
+    int64_t ord = 0;
+    int4 nrec = make_int4(0, 0, 0, 0);
+    load_node<M>(p, k, s, run, node, stream, ord, cur, cend, nrec, true, wbase);
+    AemState<M, false> a;
+    bool dead = false;
+    uint64_t key_raw = 0;  // error key, refreshed every 8 days and read 8 days later
+    for (int b = 0; b < p.nb && !dead; ++b) {
+        if ((b & 7) == 0) {
+            if (b > 0 && (__shfl(key_raw, 0, WAVE) >> 44) < (uint64_t)b) break;
+            if (lane == 0)
+                key_raw = __hip_atomic_load(&p.ctrl->err_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const int64_t day = p.T1 + b;
+        ssa_and_e1<M, false>(p, s, b, day, node, stream, ord, cur, cend, nrec, wbase, dead, t, true, a);
+        if (!dead && !M::pts(s.v, s.u, s.ld, s.gd, day)) {
+            if (lane == 0) raise_error(p.ctrl, b, PH_PTS, ord, E_PTS);
+            dead = true;
+        }
+        t.nd += lane == 0 ? 1 : 0;
+        // a state without a positive rate, an event left or a post-time step
+        // that moves it stays as it is to the end of the run
+        bool still = !dead && cur >= cend && M::pts_fixed(s.v, s.u);
+        if (still) {
+            const double w0 = M::template rate<0>(s.u, s.v, s.ld, s.gd);
+            const double w1 = M::template rate<1>(s.u, s.v, s.ld, s.gd);
+            still = w0 == 0.0 && w1 == 0.0;
+        }
+        record<M>(p, s, k, run, lane == 0, rec_off[b], still ? p.ntspan : rec_off[b + 1]);
+        if (still) {
+            t.nd += lane == 0 ? (unsigned long long)(p.nb - 1 - b) : 0ull;
+            break;
+        }
+    }
+}
+
 template <class M, bool PIPE>
 __global__ void __launch_bounds__(256) lane_kernel(KParams pa) {
     extern __shared__ unsigned long long lq_lds[];
@@ -1184,6 +1235,25 @@ __global__ void __launch_bounds__(256) lane_kernel(KParams pa) {
     unsigned long long* tally = mine + LQ_SLOTS * per_slot + LQ_SLOTS * M::NGD;
     for (int i = lane; i < per_wave; i += WAVE) mine[i] = 0ull;
     __syncthreads();
+    // the heavy nodes first, heaviest first, at a raised wave priority: the
+    // chain of steps of such a node is what the run would otherwise wait for
+    if (p.nheavy > 0) {
+        const unsigned first = gridDim.x * (blockDim.x / WAVE) / 4u;
+        Tally t;
+        for (;;) {
+            unsigned i = 0;
+            if (lane == 0) i = atomicAdd(&p.ctrl->heavy[p.group], 1u);
+            i = (unsigned)__builtin_amdgcn_readfirstlane((int)i);
+            if (i >= (unsigned)p.nheavy) break;
+            if (i < first)
+                __builtin_amdgcn_s_setprio(3);
+            else
+                __builtin_amdgcn_s_setprio(2);
+            lane_heavy<M>(p, p.heavy[i], rec_off, t);
+        }
+        __builtin_amdgcn_s_setprio(0);
+        add_counters(p.ctrl, t.tr, t.nd, t.ev, t.dr);
+    }
     // wavefront-uniform: the run of each slot (-1 free), the chunk being handed out
     int srun0 = -1, srun1 = -1;
     int cslot = -1, next = 0, stop = 0;
@@ -1763,7 +1833,7 @@ __global__ void init_kernel(KParams p, int nc, int nv, int first_rec, int reset_
     if (reset_ctrl && gtid == 0) {
         p.ctrl->err_key = NO_ERROR;
         for (int i = 0; i < 4; ++i) p.ctrl->counters[i] = 0;
-        for (int i = 0; i < MAX_GROUPS; ++i) p.ctrl->work[i] = 0;
+        for (int i = 0; i < MAX_GROUPS; ++i) p.ctrl->work[i] = p.ctrl->heavy[i] = 0;
         p.ctrl->bar_count = 0;
         p.ctrl->abort = 0;
         p.ctrl->e2done = 0;
