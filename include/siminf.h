@@ -508,24 +508,20 @@ void siminf_mlp_destroy(siminf_mlp *m);
  *   disagreement[b]  = mean over j of the members' sample standard deviation
  *                      of y (divisor members - 1; 0 for one member),
  * computed in binary64 and rounded once to float32.  Enqueued on hip_stream;
- * a device workspace of members x B x N floats is taken from the stream's
- * memory pool for the call.  1 <= members <= 64, B >= 1 (any size: members
- * run in slices of their largest batch); SIMINF_E_ARG for mismatched widths
- * or null pointers.  Uses each member's activation buffers: no other work
- * on those networks may overlap the call. */
+ * allocates nothing: each member's outputs stay in its own buffer until they
+ * are combined.  1 <= members <= 64, B >= 1 (any size: in slices of the
+ * smallest of the members' largest batches); SIMINF_E_ARG for mismatched
+ * widths or null pointers.  Uses each member's activation buffers: no other
+ * work on those networks may overlap the call. */
 int siminf_mlp_ensemble_predict(siminf_mlp *const *nets, int32_t members, const float *X, int32_t B,
                                 const float *y_mean, const float *y_std, float *Y, float *disagreement,
                                 void *hip_stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * computation as siminf_mlp_ensemble_predict, with the members x B x N
- * workspace in a fixed array of 2^22 floats (16 MiB) in device memory that
- * the library keeps on each device until the process ends; no allocation of
- * any kind.  members x B x N above 2^22 returns SIMINF_E_UNSUPPORTED before
- * any work is enqueued.  Every call on one device shares that array:
- * calls that overlap on one device (other streams or threads) race and must
- * be serialised by the caller. */
+ * computation as siminf_mlp_ensemble_predict, with a bound on its size:
+ * members x B x N above 2^22 returns SIMINF_E_UNSUPPORTED before any work is
+ * enqueued. */
 int siminf_mlp_ensemble_predict_static(siminf_mlp *const *nets, int32_t members, const float *X, int32_t B,
                                        const float *y_mean, const float *y_std, float *Y, float *disagreement,
                                        void *hip_stream);

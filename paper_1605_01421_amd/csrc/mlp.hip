@@ -11,7 +11,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <mutex>
 #include <new>
 #include <vector>
 
@@ -282,15 +281,392 @@ hipError_t gemm(GemmArgs g, hipStream_t st, float* work = nullptr, int max_slice
     return hipGetLastError();
 }
 
-__global__ void to_bf16_kernel(const float* x, uint16_t* y, long long n) {
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-        y[i] = f32_to_bf16(x[i]);
+// ---------------------------------------------------------------------------
+// networks whose every width is at most FUSE_W: whole passes in one kernel
+// ---------------------------------------------------------------------------
+// Such a network's weights (0.5 MB for the surrogate's five layers) stay in
+// every XCD's L2, and a tile of 16 rows of activations in LDS, so a workgroup
+// takes its rows through all layers, and in training through the loss and the
+// whole backward chain, without a launch or a pass over memory between them.
+//
+// Operands that come from global memory are kept in matrix-core fragments: the
+// 64 lanes' 16-byte operands of one v_mfma_f32_16x16x32_bf16, lane after lane
+// (1 KiB), zero outside the matrix, so a load needs no test and is contiguous.
+//   Wf[l]: weights for the forward product, fragment (n tile, k step)
+//   Wt[l]: weights for the input gradient, fragment (k tile, n step)
+//   Af[l], Df[l]: the layer's input and its output's gradient for the weight
+//                 gradient, fragment (step of 32 rows, feature tile)
+constexpr int FUSE_W = 256;
+constexpr int FRAG = 512;            // bf16 elements of a fragment
+constexpr int ALD = FUSE_W + 8;      // LDS row of activations: 528 bytes, 16-byte aligned
+constexpr int MAX_LAYERS = 64;
+
+__host__ __device__ inline int steps32(int n) { return (n + 31) / 32; }
+// Element (row r, reduction index k) of a fragment matrix with ks steps a row tile.
+__host__ __device__ inline size_t frag_at(int r, int k, int ks) {
+    return ((size_t)(r >> 4) * ks + (k >> 5)) * FRAG + (((k & 31) >> 3) * 16 + (r & 15)) * 8 + (k & 7);
 }
+
+// What the kernels read of a network, in device memory (set at creation).
+struct NetDesc {
+    int32_t L;
+    int32_t small;  // every width at most FUSE_W: the fused kernels' operands are there
+    int32_t dims[MAX_LAYERS + 1];
+    int64_t off[2 * MAX_LAYERS + 1];  // layer l's weights from off[2l], its bias from off[2l+1] in the arrays below
+    float *p, *g, *m, *v;             // parameters, gradients, moments
+    uint16_t *Wf[MAX_LAYERS], *Wt[MAX_LAYERS], *Wb[MAX_LAYERS], *Af[MAX_LAYERS], *Df[MAX_LAYERS];
+    float4* zs[MAX_LAYERS];           // pre-activations of the hidden layers, as the lanes hold them
+    float* Y;                         // [max_batch][dims[L]]
+};
+
+constexpr int MAX_MEMBERS = 64;
 
 struct Levels {
     float q[8];
     int nq;
 };
+
+struct FusedArgs {
+    const NetDesc* net[MAX_MEMBERS];  // blockIdx.y
+    const float* X;                   // [B][dims[0]]
+    float* Y;                         // [B][dims[L]], or null: each network's own buffer
+    const float* T;                   // training: targets [B][dims[L]]
+    double* loss;                     //           per row tile, the sum of the loss
+    Levels lv;
+    int B;
+};
+
+// A wavefront's fragments of its column tiles w, w + NW, ... of a weight
+// matrix of nt tiles and ks steps.
+template <int NT, int NW>
+__device__ __forceinline__ void load_frags(bf16x8 (&f)[NT][FUSE_W / 32], const uint16_t* W, int nt, int ks, int wave,
+                                           int lane) {
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int t = wave + j * NW;
+        const bf16x8* q = reinterpret_cast<const bf16x8*>(W) + (size_t)t * ks * 64 + lane;
+#pragma unroll
+        for (int k = 0; k < FUSE_W / 32; ++k)
+            if (t < nt && k < ks) f[j][k] = q[(size_t)k * 64];
+    }
+}
+
+template <int NT, int MT, int NW>
+__device__ __forceinline__ void tile_product(f32x4 (&acc)[NT][MT], const uint16_t* act,
+                                             const bf16x8 (&f)[NT][FUSE_W / 32], int nt, int ks, int wave, int lane) {
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int rl = lane & 15, kq = (lane >> 4) * 8;
+#pragma unroll
+    for (int k = 0; k < FUSE_W / 32; ++k) {
+        if (k >= ks) break;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            const bf16x8 a = *reinterpret_cast<const bf16x8*>(&act[(i * 16 + rl) * ALD + k * 32 + kq]);
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                if (wave + j * NW < nt) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, f[j][k], acc[j][i], 0, 0, 0);
+        }
+    }
+}
+
+__device__ __forceinline__ uint2 pack4(const uint16_t (&h)[4]) {
+    return uint2{(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
+}
+
+// One workgroup of NW wavefronts takes 16 MT rows through the network; the
+// wavefronts share a layer's column tiles.  The next layer's weights are
+// loaded while the current layer's activations are computed.  TRAIN (MT = 1):
+// keeps what the backward pass needs, then the pinball loss and its gradient,
+// and the chain dZ_{l-1} = (dZ_l W_l) * GELU'(Z_{l-1}) down to the first layer.
+// Every product runs over its reduction in steps of 32 from the first, as in
+// gemm_kernel, so the results are the same bit for bit.
+//
+// What bounds it: small batches, the chain of layers (weights from L2, the
+// products, the activations, a barrier, about 2 us each); large ones, the
+// activations (about 58 instructions each, 67 million at batch 65,536, or 100
+// us of vector work).  Measured on 8 -> 256 x 4 -> 156, before (a product
+// kernel a layer and 42 launches a training step) and after: inference at
+// 65,536 rows 275 -> 144 us; 4 members at 1,000 rows 516 -> 21 us and at 8 rows
+// 296 -> 18 us with their combination; a gradient at 4,096 rows with its
+// read-back 800 -> 275 us; a training step at 128 rows 397 -> 50 us.
+template <int NW, int MT, bool TRAIN>
+__global__ void __launch_bounds__(NW * 64) fused_kernel(FusedArgs a) {
+    static_assert(!TRAIN || MT == 1, "training takes one row tile");
+    constexpr int NT = FUSE_W / 16 / NW;
+    constexpr int BUFS = MT <= 2 ? 2 : 1;  // activations: in place needs a second barrier a layer
+    __shared__ __attribute__((aligned(16))) uint16_t act[BUFS][MT * 16 * ALD];
+    __shared__ double red[NW];
+    const NetDesc& d = *a.net[blockIdx.y];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row0 = blockIdx.x * (MT * 16);
+    const int L = d.L, B = a.B;
+    const int cl = lane & 15, rq = (lane >> 4) * 4;  // the lane's column and first row of a result tile
+    // training: where the lane's four rows of a column tile go in a fragment
+    // of 32 rows (two row tiles share it)
+    const int tile = blockIdx.x;
+    const int frow = (tile & 1) * 16 + rq;
+    const int fpos = ((frow >> 3) * 16 + cl) * 8 + (frow & 7);
+    int cur = 0;
+    {
+        const int K = d.dims[0], kp = 32 * steps32(K);
+        for (int i = tid; i < MT * 16 * kp; i += NW * 64) {
+            const int r = i / kp, k = i % kp;
+            const uint16_t h = (row0 + r < B && k < K) ? f32_to_bf16(a.X[(size_t)(row0 + r) * K + k]) : (uint16_t)0;
+            act[0][r * ALD + k] = h;
+            if constexpr (TRAIN) {
+                const int b = (tile & 1) * 16 + r;
+                d.Af[0][((size_t)(tile >> 1) * (kp / 16) + (k >> 4)) * FRAG + ((b >> 3) * 16 + (k & 15)) * 8 + (b & 7)] = h;
+            }
+        }
+    }
+    bf16x8 f[NT][FUSE_W / 32];
+    int nt = 2 * steps32(d.dims[1]), ks = steps32(d.dims[0]);
+    load_frags<NT, NW>(f, d.Wf[0], nt, ks, wave, lane);
+    double part = 0.0;
+    for (int l = 0; l < L; ++l) {
+        const int N = d.dims[l + 1];
+        const float* bias = d.p + d.off[2 * l + 1];
+        float bn[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int n = (wave + j * NW) * 16 + cl;
+            bn[j] = n < N ? bias[n] : 0.f;
+        }
+        __syncthreads();
+        f32x4 acc[NT][MT];
+        tile_product<NT, MT, NW>(acc, act[cur], f, nt, ks, wave, lane);
+        const int ntc = nt;
+        if (l + 1 < L) {
+            nt = 2 * steps32(d.dims[l + 2]);
+            ks = steps32(N);
+            load_frags<NT, NW>(f, d.Wf[l + 1], nt, ks, wave, lane);
+        } else if (TRAIN && L > 1) {
+            nt = 2 * steps32(d.dims[L - 1]);
+            ks = steps32(N);
+            load_frags<NT, NW>(f, d.Wt[L - 1], nt, ks, wave, lane);
+        }
+        if constexpr (BUFS == 1) __syncthreads();
+        else cur ^= 1;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int t = wave + j * NW, n = t * 16 + cl;
+            if (t >= ntc) continue;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                float z[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z[r] = acc[j][i][r] + bn[j];
+                if (l + 1 < L) {
+                    uint16_t h[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        h[r] = f32_to_bf16(gelu(z[r]));
+                        if (TRAIN && row0 + rq + r >= B) h[r] = 0;
+                        act[cur][(i * 16 + rq + r) * ALD + n] = h[r];
+                    }
+                    if constexpr (TRAIN) {
+                        d.zs[l][((size_t)tile * (FUSE_W / 16) + t) * 64 + lane] = float4{z[0], z[1], z[2], z[3]};
+                        *reinterpret_cast<uint2*>(d.Af[l + 1] + ((size_t)(tile >> 1) * ntc + t) * FRAG + fpos) = pack4(h);
+                    }
+                } else if constexpr (!TRAIN) {
+                    float* Y = a.Y ? a.Y : d.Y;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int b = row0 + i * 16 + rq + r;
+                        if (b < B && n < N) Y[(size_t)b * N + n] = z[r];
+                    }
+                } else {
+                    // pinball loss and its gradient dY / (B N)
+                    float q = a.lv.q[0];
+                    const int c = n % a.lv.nq;
+#pragma unroll
+                    for (int e = 1; e < 8; ++e) q = c == e ? a.lv.q[e] : q;
+                    const float total = (float)(B * N);
+                    uint16_t h[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int b = row0 + rq + r;
+                        h[r] = 0;
+                        if (b < B && n < N) {
+                            const float e = a.T[(size_t)b * N + n] - z[r];
+                            part += e > 0.f ? (double)q * e : (double)(q - 1.f) * e;
+                            h[r] = f32_to_bf16((e > 0.f ? -q : 1.f - q) / total);
+                        }
+                        act[cur][(rq + r) * ALD + n] = h[r];
+                    }
+                    *reinterpret_cast<uint2*>(d.Df[l] + ((size_t)(tile >> 1) * ntc + t) * FRAG + fpos) = pack4(h);
+                }
+            }
+        }
+    }
+    if constexpr (TRAIN) {
+        for (int l = L - 1; l > 0; --l) {
+            // dZ_l is in act[cur], Wt[l] in f: dZ_{l-1} of the columns K = dims[l]
+            float4 zp[NT];
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                if (wave + j * NW < nt) zp[j] = d.zs[l - 1][((size_t)tile * (FUSE_W / 16) + wave + j * NW) * 64 + lane];
+            __syncthreads();
+            f32x4 acc[NT][1];
+            tile_product<NT, 1, NW>(acc, act[cur], f, nt, ks, wave, lane);
+            const int ntc = nt;
+            if (l > 1) {
+                nt = 2 * steps32(d.dims[l - 1]);
+                ks = steps32(d.dims[l]);
+                load_frags<NT, NW>(f, d.Wt[l - 1], nt, ks, wave, lane);
+            }
+            cur ^= 1;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const int t = wave + j * NW, n = t * 16 + cl;
+                if (t >= ntc) continue;
+                const float z[4] = {zp[j].x, zp[j].y, zp[j].z, zp[j].w};
+                uint16_t h[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    h[r] = row0 + rq + r < B ? f32_to_bf16(acc[j][0][r] * gelu_grad(z[r])) : (uint16_t)0;
+                    act[cur][(rq + r) * ALD + n] = h[r];
+                }
+                *reinterpret_cast<uint2*>(d.Df[l - 1] + ((size_t)(tile >> 1) * ntc + t) * FRAG + fpos) = pack4(h);
+            }
+        }
+        for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
+        if (lane == 0) red[wave] = part;
+        __syncthreads();
+        if (tid == 0) {
+            double s = 0.0;
+            for (int w = 0; w < NW; ++w) s += red[w];
+            a.loss[tile] = s;
+        }
+    }
+}
+
+// Weight and bias gradients of every layer, dW_l = dZ_l^T A_{l-1} and db_l =
+// sum_b dZ_l: a workgroup takes 32 x 32 entries of one layer, its WS wavefronts
+// share the steps of 32 rows (wavefront w takes w, w + WS, ...), and their
+// sums are added in order in LDS.  The bias gradient is one more product, with
+// ones, in the workgroups of the first columns.
+template <int WS>
+__global__ void __launch_bounds__(WS * 64) fused_grad_kernel(const NetDesc* net, int B) {
+    __shared__ f32x4 red[WS > 1 ? WS : 1][6][64];
+    const NetDesc& d = *net;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int l = 0, w = blockIdx.x;
+    for (; l < d.L; ++l) {
+        const int c = steps32(d.dims[l + 1]) * steps32(d.dims[l]);
+        if (w < c) break;
+        w -= c;
+    }
+    const int N = d.dims[l + 1], K = d.dims[l];
+    const int sk = steps32(K), sn = steps32(N);
+    const int tn = w / sk, tk = w % sk;
+    const bf16x8* P = reinterpret_cast<const bf16x8*>(d.Df[l]) + (size_t)tn * 2 * 64 + lane;
+    const bf16x8* Q = reinterpret_cast<const bf16x8*>(d.Af[l]) + (size_t)tk * 2 * 64 + lane;
+    const size_t pstep = (size_t)sn * 2 * 64, qstep = (size_t)sk * 2 * 64;
+    f32x4 acc[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 ones;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
+    const int steps = steps32(B);
+    for (int s = wave; s < steps; s += WS) {
+        const bf16x8 p0 = P[s * pstep], p1 = P[s * pstep + 64], q0 = Q[s * qstep], q1 = Q[s * qstep + 64];
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p0, q0, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p0, q1, acc[1], 0, 0, 0);
+        acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p1, q0, acc[2], 0, 0, 0);
+        acc[3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p1, q1, acc[3], 0, 0, 0);
+        if (tk == 0) {
+            acc[4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p0, ones, acc[4], 0, 0, 0);
+            acc[5] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p1, ones, acc[5], 0, 0, 0);
+        }
+    }
+    if constexpr (WS > 1) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) red[wave][i][lane] = acc[i];
+        __syncthreads();
+        // wavefront i adds up product i
+        for (int i = wave; i < 6; i += WS) {
+            f32x4 s = red[0][i][lane];
+            for (int v = 1; v < WS; ++v) s += red[v][i][lane];
+            red[0][i][lane] = s;
+        }
+        __syncthreads();
+        if (wave != 0) return;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) acc[i] = red[0][i][lane];
+    }
+    float* gW = d.g + d.off[2 * l];
+    float* gb = d.g + d.off[2 * l + 1];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int n = tn * 32 + i * 16 + (lane >> 4) * 4 + r;
+            if (n >= N) continue;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int k = tk * 32 + j * 16 + (lane & 15);
+                if (k < K) gW[(size_t)n * K + k] = acc[i * 2 + j][r];
+            }
+            if (tk == 0 && (lane & 15) == 0) gb[n] = acc[4 + i][r];
+        }
+}
+
+// The bfloat16 copies of a weight (layer l, output n, input k).
+__device__ __forceinline__ void store_bf16(const NetDesc& d, int l, int n, int k, float w) {
+    const uint16_t h = f32_to_bf16(w);
+    const int N = d.dims[l + 1], K = d.dims[l];
+    if (d.small) {
+        d.Wf[l][frag_at(n, k, steps32(K))] = h;
+        d.Wt[l][frag_at(k, n, steps32(N))] = h;
+    } else {
+        d.Wb[l][(size_t)n * K + k] = h;
+    }
+}
+
+// AdamW on the float32 master parameters of every layer at once; refreshes the
+// bfloat16 copies.
+__global__ void __launch_bounds__(256) adamw_kernel(const NetDesc* net, float lr, float b1, float b2, float eps,
+                                                    float wd, float c1, float c2) {
+    const NetDesc& d = *net;
+    const long long total = d.off[2 * d.L];
+    for (long long i = blockIdx.x * 256ll + threadIdx.x; i < total; i += gridDim.x * 256ll) {
+        const float gi = d.g[i];
+        const float mi = b1 * d.m[i] + (1.f - b1) * gi;
+        const float vi = b2 * d.v[i] + (1.f - b2) * gi * gi;
+        d.m[i] = mi;
+        d.v[i] = vi;
+        const float mh = mi / c1, vh = vi / c2;
+        const float p = d.p[i];
+        const float w = p - lr * (mh / (sqrtf(vh) + eps) + wd * p);
+        d.p[i] = w;
+        int l = 0;
+        while (l + 1 < d.L && i >= d.off[2 * l + 2]) ++l;
+        if (i < d.off[2 * l + 1]) {
+            const uint32_t e = (uint32_t)(i - d.off[2 * l]), K = (uint32_t)d.dims[l];
+            store_bf16(d, l, (int)(e / K), (int)(e % K), w);
+        }
+    }
+}
+
+// Refreshes the bfloat16 copies of layer l from its master weights.
+__global__ void __launch_bounds__(256) weight_copy_kernel(const NetDesc* net, int l) {
+    const NetDesc& d = *net;
+    const uint32_t K = (uint32_t)d.dims[l];
+    const float* W = d.p + d.off[2 * l];
+    const long long total = (long long)d.dims[l + 1] * K;
+    for (long long i = blockIdx.x * 256ll + threadIdx.x; i < total; i += gridDim.x * 256ll)
+        store_bf16(d, l, (int)((uint64_t)i / K), (int)((uint64_t)i % K), W[i]);
+}
+
+__global__ void to_bf16_kernel(const float* x, uint16_t* y, long long n) {
+    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
+        y[i] = f32_to_bf16(x[i]);
+}
 
 __global__ void zero_kernel(double* x) { *x = 0.0; }
 
@@ -339,41 +715,28 @@ __global__ void colsum_finish(const float* part, int chunks, int N, float* db) {
     db[n] = s;
 }
 
-// AdamW on float32 master weights; refreshes the bfloat16 copy.
-__global__ void adamw_kernel(float* p, const float* g, float* m, float* v, uint16_t* pb, long long n, float lr,
-                             float b1, float b2, float eps, float wd, float c1, float c2) {
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        const float gi = g[i];
-        const float mi = b1 * m[i] + (1.f - b1) * gi;
-        const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-        m[i] = mi;
-        v[i] = vi;
-        const float mh = mi / c1, vh = vi / c2;
-        const float w = p[i] - lr * (mh / (sqrtf(vh) + eps) + wd * p[i]);
-        p[i] = w;
-        if (pb) pb[i] = f32_to_bf16(w);
-    }
-}
-
 // The ensemble's answer for sample b (one workgroup per sample): every
 // member's standardised output p is mapped back, y = p * y_std + y_mean
 // (binary64), Y = the members' mean, and the disagreement is the mean over
 // the outputs of the members' sample standard deviation (divisor K - 1; 0
 // for a single member).  The sums run in a fixed order.
-__global__ void __launch_bounds__(256) ensemble_combine_kernel(const float* P, int K, int B, int N,
-                                                               const float* ymean, const float* ystd, float* Y,
-                                                               float* dis) {
+struct MemberOut {
+    const float* P[MAX_MEMBERS];  // each member's standardised outputs [B][N]
+};
+
+__global__ void __launch_bounds__(256) ensemble_combine_kernel(MemberOut o, int K, int N, const float* ymean,
+                                                               const float* ystd, float* Y, float* dis) {
     __shared__ double red[256];
     const int b = blockIdx.x;
     double ssum = 0.0;
     for (int j = threadIdx.x; j < N; j += blockDim.x) {
         const double sd = ystd[j], mu = ymean[j];
         double mean = 0.0;
-        for (int k = 0; k < K; ++k) mean += (double)P[((size_t)k * B + b) * N + j] * sd + mu;
+        for (int k = 0; k < K; ++k) mean += (double)o.P[k][(size_t)b * N + j] * sd + mu;
         mean /= (double)K;
         double m2 = 0.0;
         for (int k = 0; k < K; ++k) {
-            const double d = ((double)P[((size_t)k * B + b) * N + j] * sd + mu) - mean;
+            const double d = ((double)o.P[k][(size_t)b * N + j] * sd + mu) - mean;
             m2 += d * d;
         }
         Y[(size_t)b * N + j] = (float)mean;
@@ -394,14 +757,20 @@ int grid_for(long long n) { return (int)std::max<long long>(1, std::min<long lon
 
 struct siminf_mlp {
     int L = 0, max_batch = 0, t = 0;
+    bool small = false;  // the fused kernels apply: every width at most FUSE_W
     std::vector<int> dims;
     std::vector<void*> owned;
-    std::vector<float*> W, b, gW, gb, mW, vW, mb, vb, Z;
-    std::vector<uint16_t*> Wb, A, dZ;
-    double* loss = nullptr;
-    float* Y = nullptr;
-    float* work = nullptr;   // split-K partial products of the weight gradients
-    float* cpart = nullptr;  // column-sum partials of the bias gradients
+    std::vector<float*> W, b, gW, gb;  // into the parameter and gradient arrays
+    std::vector<float*> Z;
+    std::vector<uint16_t*> Wb, A, dZ;  // general path
+    float *mom1 = nullptr, *mom2 = nullptr;
+    long long nparams = 0;
+    NetDesc host{};
+    NetDesc* desc = nullptr;           // the same in device memory
+    double* loss = nullptr;            // one sum a row tile (general path: one)
+    std::vector<double> loss_host;     // read back by siminf_mlp_backward
+    float* work = nullptr;   // general path: split-K partial products of the weight gradients
+    float* cpart = nullptr;  //               column-sum partials of the bias gradients
 };
 
 constexpr int MAX_SLICES = 16;  // split-K slices of a weight-gradient product
@@ -413,6 +782,22 @@ bool dalloc(siminf_mlp* m, size_t n, T** p) {
     if (hipMalloc((void**)p, sizeof(T) * std::max<size_t>(n, 1)) != hipSuccess) return false;
     m->owned.push_back(*p);
     return hipMemset(*p, 0, sizeof(T) * std::max<size_t>(n, 1)) == hipSuccess;
+}
+
+// The fused forward pass of K networks (all small, of the same widths in and
+// out) on the same B rows; Y null: each into its own buffer.
+hipError_t fused_forward(siminf_mlp* const* nets, int K, const float* X, int B, float* Y, hipStream_t st) {
+    FusedArgs a{};
+    for (int k = 0; k < K; ++k) a.net[k] = nets[k]->desc;
+    a.X = X;
+    a.Y = Y;
+    a.B = B;
+    const long long tiles = (long long)((B + 15) / 16) * K;
+    if (tiles <= 1024)
+        fused_kernel<16, 1, false><<<dim3((B + 15) / 16, K), 1024, 0, st>>>(a);
+    else
+        fused_kernel<8, 8, false><<<dim3((B + 127) / 128, K), 512, 0, st>>>(a);
+    return hipGetLastError();
 }
 
 // train: keep the float32 pre-activations that the backward pass needs.
@@ -444,25 +829,35 @@ int mlp_forward(siminf_mlp* m, const float* X, int B, hipStream_t st, bool train
     }
     return SIMINF_OK;
 }
-// The ensemble prediction into the workspace `work` (members x B x N
-// floats): each member's forward pass in slices of its largest batch, its
-// outputs copied into its part of the workspace, then the combination.
+
+// The ensemble prediction: in slices of the members' smallest largest batch,
+// every member's forward pass into its own output buffer (the fused ones in
+// one launch), then the combination from those buffers.
 int ensemble_predict(siminf_mlp* const* nets, int K, const float* X, int B, const float* ymean, const float* ystd,
-                     float* Y, float* dis, hipStream_t st, float* work) {
+                     float* Y, float* dis, hipStream_t st) {
     const int din = nets[0]->dims[0], N = nets[0]->dims[nets[0]->L];
+    int slice = nets[0]->max_batch;
+    siminf_mlp* fused[MAX_MEMBERS];
+    int nf = 0;
+    MemberOut o{};
     for (int k = 0; k < K; ++k) {
-        siminf_mlp* m = nets[k];
-        for (int b0 = 0; b0 < B; b0 += m->max_batch) {
-            const int bs = std::min(m->max_batch, B - b0);
-            const int rc = mlp_forward(m, X + (size_t)b0 * din, bs, st, false);
-            if (rc) return rc;
-            if (hipMemcpyAsync(work + ((size_t)k * B + b0) * N, m->Z[m->L - 1], sizeof(float) * (size_t)bs * N,
-                               hipMemcpyDeviceToDevice, st) != hipSuccess)
-                return SIMINF_E_DEVICE;
-        }
+        slice = std::min(slice, nets[k]->max_batch);
+        if (nets[k]->small) fused[nf++] = nets[k];
+        o.P[k] = nets[k]->small ? nets[k]->host.Y : nets[k]->Z[nets[k]->L - 1];
     }
-    ensemble_combine_kernel<<<B, 256, 0, st>>>(work, K, B, N, ymean, ystd, Y, dis);
-    return hipGetLastError() == hipSuccess ? SIMINF_OK : SIMINF_E_DEVICE;
+    for (int b0 = 0; b0 < B; b0 += slice) {
+        const int bs = std::min(slice, B - b0);
+        const float* Xs = X + (size_t)b0 * din;
+        if (nf > 0 && fused_forward(fused, nf, Xs, bs, nullptr, st) != hipSuccess) return SIMINF_E_DEVICE;
+        for (int k = 0; k < K; ++k)
+            if (!nets[k]->small) {
+                const int rc = mlp_forward(nets[k], Xs, bs, st, false);
+                if (rc) return rc;
+            }
+        ensemble_combine_kernel<<<bs, 256, 0, st>>>(o, K, N, ymean, ystd, Y + (size_t)b0 * N, dis + b0);
+        if (hipGetLastError() != hipSuccess) return SIMINF_E_DEVICE;
+    }
+    return SIMINF_OK;
 }
 
 int ensemble_check(siminf_mlp* const* nets, int K, const float* X, int B, const float* ymean, const float* ystd,
@@ -475,36 +870,8 @@ int ensemble_check(siminf_mlp* const* nets, int K, const float* X, int B, const 
     }
     return SIMINF_OK;
 }
-// The workspace of siminf_mlp_ensemble_predict_static, for callers that
-// cannot allocate: a fixed array in device memory, one per device (each GPU
-// the library runs on holds it until the process ends).  In host code the
-// array's name is not a device address: its address on the current device
-// comes from hipGetSymbolAddress, taken once per device.
-constexpr size_t SCRATCH_FLOATS = (size_t)1 << 22;  // 16 MiB
-__device__ __align__(256) float scratch[SCRATCH_FLOATS];
-
-constexpr int SCRATCH_DEVICES = 64;
-std::mutex scratch_mutex;
-float* scratch_ptr[SCRATCH_DEVICES] = {};
-
-// The current device's copy of `scratch`, or nullptr (and *rc set).
-float* scratch_on_current_device(int* rc) {
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= SCRATCH_DEVICES) {
-        *rc = SIMINF_E_DEVICE;
-        return nullptr;
-    }
-    std::lock_guard<std::mutex> lock(scratch_mutex);
-    if (!scratch_ptr[dev]) {
-        void* ptr = nullptr;
-        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) {
-            *rc = SIMINF_E_DEVICE;
-            return nullptr;
-        }
-        scratch_ptr[dev] = (float*)ptr;
-    }
-    return scratch_ptr[dev];
-}
+// Largest members x rows x outputs of siminf_mlp_ensemble_predict_static.
+constexpr size_t STATIC_FLOATS = (size_t)1 << 22;
 }  // namespace
 
 extern "C" {
@@ -523,30 +890,60 @@ int siminf_mlp_create(int32_t nlayers, const int32_t* dims, int32_t max_batch, s
     m->b.resize(nlayers);
     m->gW.resize(nlayers);
     m->gb.resize(nlayers);
-    m->mW.resize(nlayers);
-    m->vW.resize(nlayers);
-    m->mb.resize(nlayers);
-    m->vb.resize(nlayers);
     m->Z.resize(nlayers);
     m->Wb.resize(nlayers);
     m->dZ.resize(nlayers);
     m->A.resize(nlayers);
-    bool ok = true;
-    for (int l = 0; l < nlayers; ++l) {
-        const size_t nw = (size_t)dims[l + 1] * dims[l], nb = dims[l + 1], nz = (size_t)max_batch * dims[l + 1];
-        ok = ok && dalloc(m, nw, &m->W[l]) && dalloc(m, nb, &m->b[l]) && dalloc(m, nw, &m->gW[l]) &&
-             dalloc(m, nb, &m->gb[l]) && dalloc(m, nw, &m->mW[l]) && dalloc(m, nw, &m->vW[l]) &&
-             dalloc(m, nb, &m->mb[l]) && dalloc(m, nb, &m->vb[l]) && dalloc(m, nz, &m->Z[l]) &&
-             dalloc(m, nw, &m->Wb[l]) && dalloc(m, nz, &m->dZ[l]) &&
-             dalloc(m, (size_t)max_batch * dims[l], &m->A[l]);
-    }
+    NetDesc& d = m->host;
+    d.L = nlayers;
     size_t wmax = 1, nmax = 1;
+    int widest = 1;
+    for (int l = 0; l <= nlayers; ++l) {
+        d.dims[l] = dims[l];
+        widest = std::max(widest, dims[l]);
+    }
     for (int l = 0; l < nlayers; ++l) {
-        wmax = std::max(wmax, (size_t)dims[l + 1] * dims[l]);
+        const size_t nw = (size_t)dims[l + 1] * dims[l];
+        d.off[2 * l] = m->nparams;
+        d.off[2 * l + 1] = m->nparams + (long long)nw;
+        m->nparams += (long long)nw + dims[l + 1];
+        wmax = std::max(wmax, nw);
         nmax = std::max(nmax, (size_t)dims[l + 1]);
     }
-    ok = ok && dalloc(m, 1, &m->loss) && dalloc(m, (size_t)MAX_SLICES * wmax, &m->work) &&
-         dalloc(m, (size_t)((max_batch + 255) / 256) * nmax, &m->cpart);
+    d.off[2 * nlayers] = m->nparams;
+    // the fused kernels hold a row tile's activations in LDS and a layer's
+    // share of weights in registers; they apply to every batch size
+    m->small = widest <= FUSE_W;
+    d.small = m->small ? 1 : 0;
+    const size_t np = (size_t)m->nparams, rows = (size_t)max_batch;
+    bool ok = dalloc(m, np, &d.p) && dalloc(m, np, &d.g) && dalloc(m, np, &d.m) && dalloc(m, np, &d.v);
+    m->mom1 = d.m;
+    m->mom2 = d.v;
+    for (int l = 0; ok && l < nlayers; ++l) {
+        m->W[l] = d.p + d.off[2 * l];
+        m->b[l] = d.p + d.off[2 * l + 1];
+        m->gW[l] = d.g + d.off[2 * l];
+        m->gb[l] = d.g + d.off[2 * l + 1];
+        const size_t N = dims[l + 1], K = dims[l];
+        if (m->small) {
+            const size_t sn = steps32(N), sk = steps32(K), sb = steps32(max_batch);
+            ok = dalloc(m, 2 * sn * sk * FRAG, &d.Wf[l]) && dalloc(m, 2 * sn * sk * FRAG, &d.Wt[l]) &&
+                 dalloc(m, 2 * sb * sk * FRAG, &d.Af[l]) && dalloc(m, 2 * sb * sn * FRAG, &d.Df[l]) &&
+                 (l + 1 == nlayers || dalloc(m, 2 * sb * (FUSE_W / 16) * 64, &d.zs[l]));
+        } else {
+            ok = dalloc(m, rows * N, &m->Z[l]) && dalloc(m, N * K, &m->Wb[l]) && dalloc(m, rows * N, &m->dZ[l]) &&
+                 dalloc(m, rows * K, &m->A[l]);
+            d.Wb[l] = m->Wb[l];
+        }
+    }
+    if (m->small) {
+        ok = ok && dalloc(m, rows * dims[nlayers], &d.Y) && dalloc(m, 2 * (size_t)steps32(max_batch), &m->loss);
+    } else {
+        ok = ok && dalloc(m, 1, &m->loss) && dalloc(m, (size_t)MAX_SLICES * wmax, &m->work) &&
+             dalloc(m, (rows + 255) / 256 * nmax, &m->cpart);
+    }
+    m->loss_host.assign(m->small ? 2 * (size_t)steps32(max_batch) : 1, 0.0);
+    ok = ok && dalloc(m, 1, &m->desc) && hipMemcpy(m->desc, &d, sizeof(NetDesc), hipMemcpyHostToDevice) == hipSuccess;
     if (!ok) return SIMINF_E_ALLOC;
     return SIMINF_OK;
 }
@@ -554,14 +951,15 @@ int siminf_mlp_create(int32_t nlayers, const int32_t* dims, int32_t max_batch, s
 int siminf_mlp_set_params(siminf_mlp* m, int32_t layer, const float* W, const float* b) {
     if (!m || layer < 0 || layer >= m->L || !W || !b) return SIMINF_E_ARG;
     const size_t nw = (size_t)m->dims[layer + 1] * m->dims[layer], nb = m->dims[layer + 1];
-    std::vector<uint16_t> wb(nw);
-    for (size_t i = 0; i < nw; ++i) wb[i] = f32_to_bf16(W[i]);
+    const long long at = m->host.off[2 * layer];
+    // the layer's weights and bias are neighbours in every array
     if (hipMemcpy(m->W[layer], W, nw * 4, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(m->b[layer], b, nb * 4, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(m->Wb[layer], wb.data(), nw * 2, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemset(m->mW[layer], 0, nw * 4) != hipSuccess || hipMemset(m->vW[layer], 0, nw * 4) != hipSuccess ||
-        hipMemset(m->mb[layer], 0, nb * 4) != hipSuccess || hipMemset(m->vb[layer], 0, nb * 4) != hipSuccess)
+        hipMemset(m->mom1 + at, 0, (nw + nb) * 4) != hipSuccess ||
+        hipMemset(m->mom2 + at, 0, (nw + nb) * 4) != hipSuccess)
         return SIMINF_E_DEVICE;
+    weight_copy_kernel<<<grid_for((long long)nw), 256, 0, nullptr>>>(m->desc, layer);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) return SIMINF_E_DEVICE;
     m->t = 0;
     return SIMINF_OK;
 }
@@ -588,6 +986,7 @@ int siminf_mlp_get_grads(const siminf_mlp* m, int32_t layer, float* dW, float* d
 int siminf_mlp_forward(siminf_mlp* m, const float* X, int32_t B, float* Y, void* hip_stream) {
     if (!m || !X || !Y || B < 1 || B > m->max_batch) return SIMINF_E_ARG;
     hipStream_t st = (hipStream_t)hip_stream;
+    if (m->small) return fused_forward(&m, 1, X, B, Y, st) == hipSuccess ? SIMINF_OK : SIMINF_E_DEVICE;
     const int rc = mlp_forward(m, X, B, st, false);
     if (rc) return rc;
     const size_t ny = (size_t)B * m->dims[m->L];
@@ -602,53 +1001,79 @@ int siminf_mlp_backward(siminf_mlp* m, const float* X, const float* T, int32_t B
     Levels lv{};
     lv.nq = nq;
     for (int i = 0; i < nq; ++i) lv.q[i] = (float)probs[i];
-    zero_kernel<<<1, 1, 0, st>>>(m->loss);
-    int rc = mlp_forward(m, X, B, st, true);
-    if (rc) return rc;
     const int L = m->L, Nout = m->dims[L];
-    pinball_kernel<<<std::min(grid_for((long long)B * Nout), 512), 256, 0, st>>>(m->Z[L - 1], T, B, Nout, lv, m->dZ[L - 1],
-                                                                 m->loss);
-    if (hipGetLastError() != hipSuccess) return SIMINF_E_DEVICE;
-    for (int l = L - 1; l >= 0; --l) {
-        const int N = m->dims[l + 1], K = m->dims[l];
-        // dW_l[N,K] = dZ_l^T A_{l-1}: reduction over the batch
-        GemmArgs g{};
-        g.M = N;
-        g.N = K;
-        g.K = B;
-        g.A = m->dZ[l];
-        g.lda = N;
-        g.B = m->A[l];
-        g.ldb = K;
-        g.Cf = m->gW[l];
-        g.ldc = K;
-        if (gemm<true, true, EPI_STORE>(g, st, m->work, MAX_SLICES) != hipSuccess) return SIMINF_E_DEVICE;
-        const int chunks = (B + 255) / 256;
-        colsum_kernel<<<dim3((N + 63) / 64, chunks), 256, 0, st>>>(m->dZ[l], B, N, N, m->cpart);
-        colsum_finish<<<(N + 255) / 256, 256, 0, st>>>(m->cpart, chunks, N, m->gb[l]);
+    int sums = 1;  // partial sums of the loss
+    if (m->small) {
+        // a launch for the rows' forward and backward chain, one for the
+        // gradients' reductions over the batch
+        FusedArgs a{};
+        a.net[0] = m->desc;
+        a.X = X;
+        a.T = T;
+        a.loss = m->loss;
+        a.lv = lv;
+        a.B = B;
+        sums = 2 * steps32(B);
+        fused_kernel<16, 1, true><<<sums, 1024, 0, st>>>(a);
+        int tiles = 0;
+        for (int l = 0; l < L; ++l) tiles += steps32(m->dims[l + 1]) * steps32(m->dims[l]);
+        if (B <= 256)
+            fused_grad_kernel<1><<<tiles, 64, 0, st>>>(m->desc, B);
+        else if (B <= 1024)
+            fused_grad_kernel<4><<<tiles, 256, 0, st>>>(m->desc, B);
+        else
+            fused_grad_kernel<8><<<tiles, 512, 0, st>>>(m->desc, B);
         if (hipGetLastError() != hipSuccess) return SIMINF_E_DEVICE;
-        if (l > 0) {
-            // dZ_{l-1}[B,K] = (dZ_l W_l) * GELU'(Z_{l-1})
-            GemmArgs d{};
-            d.M = B;
-            d.N = K;
-            d.K = N;
-            d.A = m->dZ[l];
-            d.lda = N;
-            d.B = m->Wb[l];
-            d.ldb = K;
-            d.Cb = m->dZ[l - 1];
-            d.ldcb = K;
-            d.Zp = m->Z[l - 1];
-            d.ldzp = K;
-            if (gemm<false, true, EPI_DGELU>(d, st) != hipSuccess) return SIMINF_E_DEVICE;
+    } else {
+        zero_kernel<<<1, 1, 0, st>>>(m->loss);
+        const int rc = mlp_forward(m, X, B, st, true);
+        if (rc) return rc;
+        pinball_kernel<<<std::min(grid_for((long long)B * Nout), 512), 256, 0, st>>>(m->Z[L - 1], T, B, Nout, lv, m->dZ[L - 1],
+                                                                     m->loss);
+        if (hipGetLastError() != hipSuccess) return SIMINF_E_DEVICE;
+        for (int l = L - 1; l >= 0; --l) {
+            const int N = m->dims[l + 1], K = m->dims[l];
+            // dW_l[N,K] = dZ_l^T A_{l-1}: reduction over the batch
+            GemmArgs g{};
+            g.M = N;
+            g.N = K;
+            g.K = B;
+            g.A = m->dZ[l];
+            g.lda = N;
+            g.B = m->A[l];
+            g.ldb = K;
+            g.Cf = m->gW[l];
+            g.ldc = K;
+            if (gemm<true, true, EPI_STORE>(g, st, m->work, MAX_SLICES) != hipSuccess) return SIMINF_E_DEVICE;
+            const int chunks = (B + 255) / 256;
+            colsum_kernel<<<dim3((N + 63) / 64, chunks), 256, 0, st>>>(m->dZ[l], B, N, N, m->cpart);
+            colsum_finish<<<(N + 255) / 256, 256, 0, st>>>(m->cpart, chunks, N, m->gb[l]);
+            if (hipGetLastError() != hipSuccess) return SIMINF_E_DEVICE;
+            if (l > 0) {
+                // dZ_{l-1}[B,K] = (dZ_l W_l) * GELU'(Z_{l-1})
+                GemmArgs d{};
+                d.M = B;
+                d.N = K;
+                d.K = N;
+                d.A = m->dZ[l];
+                d.lda = N;
+                d.B = m->Wb[l];
+                d.ldb = K;
+                d.Cb = m->dZ[l - 1];
+                d.ldcb = K;
+                d.Zp = m->Z[l - 1];
+                d.ldzp = K;
+                if (gemm<false, true, EPI_DGELU>(d, st) != hipSuccess) return SIMINF_E_DEVICE;
+            }
         }
     }
     if (loss) {
-        double s = 0.0;
-        if (hipMemcpyAsync(&s, m->loss, sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
+        if (hipMemcpyAsync(m->loss_host.data(), m->loss, sizeof(double) * sums, hipMemcpyDeviceToHost, st) !=
+                hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
             return SIMINF_E_DEVICE;
+        double s = 0.0;
+        for (int i = 0; i < sums; ++i) s += m->loss_host[i];
         *loss = s / ((double)B * Nout);
     }
     return SIMINF_OK;
@@ -660,15 +1085,8 @@ int siminf_mlp_adamw(siminf_mlp* m, float lr, float beta1, float beta2, float ep
     hipStream_t st = (hipStream_t)hip_stream;
     m->t += 1;
     const float c1 = 1.f - powf(beta1, (float)m->t), c2 = 1.f - powf(beta2, (float)m->t);
-    for (int l = 0; l < m->L; ++l) {
-        const long long nw = (long long)m->dims[l + 1] * m->dims[l], nb = m->dims[l + 1];
-        adamw_kernel<<<grid_for(nw), 256, 0, st>>>(m->W[l], m->gW[l], m->mW[l], m->vW[l], m->Wb[l], nw, lr, beta1,
-                                                  beta2, eps, weight_decay, c1, c2);
-        adamw_kernel<<<grid_for(nb), 256, 0, st>>>(m->b[l], m->gb[l], m->mb[l], m->vb[l], nullptr, nb, lr, beta1,
-                                                  beta2, eps, weight_decay, c1, c2);
-        if (hipGetLastError() != hipSuccess) return SIMINF_E_DEVICE;
-    }
-    return SIMINF_OK;
+    adamw_kernel<<<grid_for(m->nparams), 256, 0, st>>>(m->desc, lr, beta1, beta2, eps, weight_decay, c1, c2);
+    return hipGetLastError() == hipSuccess ? SIMINF_OK : SIMINF_E_DEVICE;
 }
 
 void siminf_mlp_destroy(siminf_mlp* m) {
@@ -681,27 +1099,18 @@ void siminf_mlp_destroy(siminf_mlp* m) {
 int siminf_mlp_ensemble_predict(siminf_mlp* const* nets, int32_t members, const float* X, int32_t B,
                                 const float* y_mean, const float* y_std, float* Y, float* disagreement,
                                 void* hip_stream) {
-    int rc = ensemble_check(nets, members, X, B, y_mean, y_std, Y, disagreement);
+    const int rc = ensemble_check(nets, members, X, B, y_mean, y_std, Y, disagreement);
     if (rc) return rc;
-    hipStream_t st = (hipStream_t)hip_stream;
-    const size_t n = (size_t)members * B * nets[0]->dims[nets[0]->L];
-    float* work = nullptr;
-    if (hipMallocAsync((void**)&work, sizeof(float) * n, st) != hipSuccess) return SIMINF_E_ALLOC;
-    rc = ensemble_predict(nets, members, X, B, y_mean, y_std, Y, disagreement, st, work);
-    if (hipFreeAsync(work, st) != hipSuccess && rc == SIMINF_OK) rc = SIMINF_E_DEVICE;
-    return rc;
+    return ensemble_predict(nets, members, X, B, y_mean, y_std, Y, disagreement, (hipStream_t)hip_stream);
 }
 
 int siminf_mlp_ensemble_predict_static(siminf_mlp* const* nets, int32_t members, const float* X, int32_t B,
                                        const float* y_mean, const float* y_std, float* Y, float* disagreement,
                                        void* hip_stream) {
-    int rc = ensemble_check(nets, members, X, B, y_mean, y_std, Y, disagreement);
+    const int rc = ensemble_check(nets, members, X, B, y_mean, y_std, Y, disagreement);
     if (rc) return rc;
-    const size_t n = (size_t)members * B * nets[0]->dims[nets[0]->L];
-    if (n > SCRATCH_FLOATS) return SIMINF_E_UNSUPPORTED;
-    float* work = scratch_on_current_device(&rc);
-    if (!work) return rc;
-    return ensemble_predict(nets, members, X, B, y_mean, y_std, Y, disagreement, (hipStream_t)hip_stream, work);
+    if ((size_t)members * B * nets[0]->dims[nets[0]->L] > STATIC_FLOATS) return SIMINF_E_UNSUPPORTED;
+    return ensemble_predict(nets, members, X, B, y_mean, y_std, Y, disagreement, (hipStream_t)hip_stream);
 }
 
 int siminf_gemm_bf16(int32_t M, int32_t N, int32_t K, const uint16_t* A, int32_t lda, int32_t a_trans,
