@@ -20,6 +20,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int BM = 128, BN = 128;  // output tile per workgroup of 256 threads
 constexpr int KT = 32;             // K per matrix-core step
@@ -43,6 +44,97 @@ __host__ __device__ inline float bf16_to_f32(uint16_t h) {
 __device__ inline float gelu(float z) { return 0.5f * z * erfcf(-z * 0.70710678118654752f); }
 __device__ inline float gelu_grad(float z) {
     return 0.5f * erfcf(-z * 0.70710678118654752f) + z * 0.39894228040143268f * expf(-0.5f * z * z);
+}
+
+// GELU and its derivative are needed rounded to bfloat16, 256 times coarser
+// than float32, so most of the time a cheaper value with a known error settles
+// the rounding: where every value within the error of the cheap one rounds to
+// the same bfloat16, that is the exact path's result too, and the wavefront
+// takes the exact path only for the others (a twelfth of the groups of four
+// for normally distributed z).  The results are those of f32_to_bf16(gelu(z))
+// and f32_to_bf16(v * gelu_grad(z)) bit for bit, shown over all 2^32 values of
+// z; about 26 and 40 instructions an element instead of 65 and 87.
+//
+// log2 Phi(-x) on [0, FAST_X] as a polynomial (least weighted maximum error
+// 2.3e-7, fitted to the function in 40 digits): Phi(-x) = 2^that is within
+// 2^-18.9 relative there, and within 2^-21 for x < 2.
+constexpr float FAST_X = 5.25f;
+__device__ __forceinline__ float phi_below(float x) {  // Phi(-x), 0 <= x <= FAST_X
+    float h = -0x1.a1103ep-26f;
+    h = __builtin_fmaf(h, x, 0x1.86ce82p-21f);
+    h = __builtin_fmaf(h, x, -0x1.3bf668p-17f);
+    h = __builtin_fmaf(h, x, 0x1.1740e0p-14f);
+    h = __builtin_fmaf(h, x, -0x1.fd2c9ap-13f);
+    h = __builtin_fmaf(h, x, -0x1.599feep-14f);
+    h = __builtin_fmaf(h, x, 0x1.ce5c30p-8f);
+    h = __builtin_fmaf(h, x, -0x1.ae3e0ap-5f);
+    h = __builtin_fmaf(h, x, -0x1.d636acp-2f);
+    h = __builtin_fmaf(h, x, -0x1.26af02p+0f);
+    h = __builtin_fmaf(h, x, -0x1.fffffep-1f);
+    return __builtin_amdgcn_exp2f(h);
+}
+__device__ __forceinline__ uint32_t f32_bits(float f) {
+    uint32_t u;
+    __builtin_memcpy(&u, &f, 4);
+    return u;
+}
+
+// The cheap GELU; within gelu_ulps(z) float32 ulps of gelu(z) unless z is
+// below -FAST_X or not a number.
+__device__ __forceinline__ float gelu_cheap(float z) {
+    const float x = __builtin_amdgcn_fmed3f(__builtin_fabsf(z), 0.f, FAST_X);
+    // z - x Phi(-x) for z >= 0, -x Phi(-x) for z < 0 (the zero keeps z's sign)
+    return __builtin_fmaf(-x, phi_below(x), z < 0.f ? -0.f : z);
+}
+__device__ __forceinline__ uint32_t gelu_ulps(float z) { return z < -2.f ? 60u : 14u; }
+
+// h[i] = bfloat16 of gelu(z[i])
+template <int NR>
+__device__ __forceinline__ void gelu_bf16(const float (&z)[NR], uint16_t (&h)[NR]) {
+    uint32_t exact = 0;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        // halfway cases sit where the low half, plus 0x8000, wraps to 0
+        const uint32_t e = gelu_ulps(z[i]);
+        const uint32_t w = f32_bits(gelu_cheap(z[i])) + 0x8000u;
+        exact |= (uint32_t)(((w + e) & 0xFFFFu) <= 2u * e) | (uint32_t)!(z[i] >= -FAST_X);
+        h[i] = (uint16_t)(w >> 16);
+    }
+    if (exact) {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) h[i] = f32_to_bf16(gelu(z[i]));
+    }
+}
+
+// The cheap derivative, within GRAD_ERR of gelu_grad(z) for |z| <= FAST_X.
+constexpr float GRAD_ERR = 0x1p-20f;
+__device__ __forceinline__ float gelu_grad_cheap(float z) {
+    const float x = __builtin_fabsf(z);
+    const float q = phi_below(__builtin_amdgcn_fmed3f(x, 0.f, FAST_X));
+    const float phi = __builtin_amdgcn_exp2f(z * z * -0.72134752044448170f);
+    return __builtin_fmaf(z * 0.39894228040143268f, phi, z < 0.f ? q : 1.f - q);
+}
+__device__ __forceinline__ uint32_t bf16_round(float f) {  // bfloat16 bits of a number in the high half
+    const uint32_t u = f32_bits(f);
+    return u + 0x7FFFu + ((u >> 16) & 1u);
+}
+// h[i] = bfloat16 of v[i] * gelu_grad(z[i])
+template <int NR>
+__device__ __forceinline__ void gelu_grad_bf16(const float (&v)[NR], const float (&z)[NR], uint16_t (&h)[NR]) {
+    uint32_t exact = 0;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        // rounding is monotone: if both ends agree, so does all between
+        const float g = gelu_grad_cheap(z[i]);
+        const uint32_t a = bf16_round(v[i] * (g - GRAD_ERR)), b = bf16_round(v[i] * (g + GRAD_ERR));
+        exact |= (a ^ b) >> 16 | (uint32_t)!(__builtin_fabsf(z[i]) <= FAST_X) |
+                 (uint32_t)!(__builtin_fabsf(v[i]) <= 0x1p120f);
+        h[i] = (uint16_t)(a >> 16);
+    }
+    if (exact) {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) h[i] = f32_to_bf16(v[i] * gelu_grad(z[i]));
+    }
 }
 
 // Epilogues: float32 result (+ bias); GELU with the pre-activation kept
@@ -292,14 +384,19 @@ hipError_t gemm(GemmArgs g, hipStream_t st, float* work = nullptr, int max_slice
 // Operands that come from global memory are kept in matrix-core fragments: the
 // 64 lanes' 16-byte operands of one v_mfma_f32_16x16x32_bf16, lane after lane
 // (1 KiB), zero outside the matrix, so a load needs no test and is contiguous.
-//   Wf[l]: weights for the forward product, fragment (n tile, k step)
-//   Wt[l]: weights for the input gradient, fragment (k tile, n step)
-//   Af[l], Df[l]: the layer's input and its output's gradient for the weight
-//                 gradient, fragment (step of 32 rows, feature tile)
+//   Wf: weights for the forward product, fragment (n tile, k step) of each layer
+//   Wt: weights for the input gradient, fragment (k tile, n step)
+//   Af, Df: each layer's input and its output's gradient for the weight
+//           gradient, fragment (step of 32 rows, feature tile)
 constexpr int FUSE_W = 256;
+constexpr int FUSE_KS = FUSE_W / 32;  // steps of the widest reduction
+constexpr int FUSE_L = 16;           // layers
 constexpr int FRAG = 512;            // bf16 elements of a fragment
 constexpr int ALD = FUSE_W + 8;      // LDS row of activations: 528 bytes, 16-byte aligned
-constexpr int MAX_LAYERS = 64;
+constexpr int MAX_LAYERS = 64, MAX_MEMBERS = 64;
+
+// A pointer into device memory, known to be one (loads through it are not flat).
+#define SIMINF_GLOBAL __attribute__((address_space(1)))
 
 __host__ __device__ inline int steps32(int n) { return (n + 31) / 32; }
 // Element (row r, reduction index k) of a fragment matrix with ks steps a row tile.
@@ -307,146 +404,248 @@ __host__ __device__ inline size_t frag_at(int r, int k, int ks) {
     return ((size_t)(r >> 4) * ks + (k >> 5)) * FRAG + (((k & 31) >> 3) * 16 + (r & 15)) * 8 + (k & 7);
 }
 
-// What the kernels read of a network, in device memory (set at creation).
-struct NetDesc {
+// What the fused kernels read of a network, by value in their arguments: the
+// layers' parts of each array follow each other, so their places come from the
+// widths without another load.
+struct NetArg {
+    const uint16_t *Wf, *Wt;
+    const float* p;        // W_0, b_0, W_1, b_1, ...
+    uint16_t *Af, *Df;
+    float* zs;             // pre-activations of the hidden layers, as the lanes hold them
+    float* Y;              // output rows
     int32_t L;
-    int32_t small;  // every width at most FUSE_W: the fused kernels' operands are there
-    int32_t dims[MAX_LAYERS + 1];
-    int64_t off[2 * MAX_LAYERS + 1];  // layer l's weights from off[2l], its bias from off[2l+1] in the arrays below
-    float *p, *g, *m, *v;             // parameters, gradients, moments
-    uint16_t *Wf[MAX_LAYERS], *Wt[MAX_LAYERS], *Wb[MAX_LAYERS], *Af[MAX_LAYERS], *Df[MAX_LAYERS];
-    float4* zs[MAX_LAYERS];           // pre-activations of the hidden layers, as the lanes hold them
-    float* Y;                         // [max_batch][dims[L]]
+    int32_t rows32;        // steps of 32 rows that Af, Df and zs hold
+    int32_t dims[FUSE_L + 1];
 };
-
-constexpr int MAX_MEMBERS = 64;
 
 struct Levels {
     float q[8];
     int nq;
 };
 
+constexpr int FUSE_NETS = 16;  // networks of one launch
 struct FusedArgs {
-    const NetDesc* net[MAX_MEMBERS];  // blockIdx.y
-    const float* X;                   // [B][dims[0]]
-    float* Y;                         // [B][dims[L]], or null: each network's own buffer
-    const float* T;                   // training: targets [B][dims[L]]
-    double* loss;                     //           per row tile, the sum of the loss
+    NetArg net[FUSE_NETS];  // blockIdx.y
+    const float* X;         // [B][dims[0]]
+    const float* T;         // training: targets [B][dims[L]]
+    double* loss;           //           per row tile, the sum of the loss
     Levels lv;
     int B;
 };
 
 // A wavefront's fragments of its column tiles w, w + NW, ... of a weight
-// matrix of nt tiles and ks steps.
+// matrix of nt tiles and ks steps (tiles and steps past the end repeat the
+// last: no test, and their products are not used).
 template <int NT, int NW>
-__device__ __forceinline__ void load_frags(bf16x8 (&f)[NT][FUSE_W / 32], const uint16_t* W, int nt, int ks, int wave,
-                                           int lane) {
+__device__ __forceinline__ void load_frags(bf16x8 (&f)[NT][FUSE_KS], const SIMINF_GLOBAL bf16x8* W, int nt, int ks,
+                                           int wave, int lane) {
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-        const int t = wave + j * NW;
-        const bf16x8* q = reinterpret_cast<const bf16x8*>(W) + (size_t)t * ks * 64 + lane;
+        const int t = min(wave + j * NW, nt - 1);
+        const SIMINF_GLOBAL bf16x8* q = W + t * ks * 64;
 #pragma unroll
-        for (int k = 0; k < FUSE_W / 32; ++k)
-            if (t < nt && k < ks) f[j][k] = q[(size_t)k * 64];
+        for (int k = 0; k < FUSE_KS; ++k) f[j][k] = (q + min(k, ks - 1) * 64)[lane];
     }
 }
 
-template <int NT, int MT, int NW>
-__device__ __forceinline__ void tile_product(f32x4 (&acc)[NT][MT], const uint16_t* act,
-                                             const bf16x8 (&f)[NT][FUSE_W / 32], int nt, int ks, int wave, int lane) {
+// The products of the wavefront's column tiles with the row tiles in LDS, over
+// KS steps in order.  With R < 16 rows a tile, the product's four rows of a
+// lane group q are the tile's rows q R/4, ..., repeated.
+template <int NT, int MT, int R, int KS>
+__device__ __forceinline__ void tile_product(f32x4 (&acc)[NT][MT], const uint16_t* act, const bf16x8 (&f)[NT][FUSE_KS],
+                                             int lane) {
+    constexpr int NR = R / 4;
+    const uint16_t* row = act + (((lane & 15) >> 2) * NR + (lane & 3) % NR) * ALD + (lane >> 4) * 8;
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
+    for (int i = 0; i < MT; ++i) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const bf16x8 a = *reinterpret_cast<const bf16x8*>(row + i * R * ALD + k * 32);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, f[j][k], acc[j][i], 0, 0, 0);
+        }
+    }
+}
+// The same with the weights loaded step by step, two steps ahead (several row
+// tiles a workgroup: the registers go to the products).
+template <int NT, int MT, int NW>
+__device__ __forceinline__ void stream_product(f32x4 (&acc)[NT][MT], const uint16_t* act,
+                                               const SIMINF_GLOBAL bf16x8* W, int nt, int ks, int wave, int lane) {
+    const uint16_t* row = act + (lane & 15) * ALD + (lane >> 4) * 8;
+    const SIMINF_GLOBAL bf16x8* q[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        q[j] = W + min(wave + j * NW, nt - 1) * ks * 64;
 #pragma unroll
         for (int i = 0; i < MT; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int rl = lane & 15, kq = (lane >> 4) * 8;
+    }
+    bf16x8 f[2][NT];
+    auto load = [&](int k, bf16x8 (&x)[NT]) {
 #pragma unroll
-    for (int k = 0; k < FUSE_W / 32; ++k) {
-        if (k >= ks) break;
+        for (int j = 0; j < NT; ++j) x[j] = (q[j] + min(k, ks - 1) * 64)[lane];
+    };
+    auto step = [&](int k, const bf16x8 (&x)[NT]) {
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(&act[(i * 16 + rl) * ALD + k * 32 + kq]);
+            const bf16x8 a = *reinterpret_cast<const bf16x8*>(row + i * 16 * ALD + k * 32);
 #pragma unroll
-            for (int j = 0; j < NT; ++j)
-                if (wave + j * NW < nt) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, f[j][k], acc[j][i], 0, 0, 0);
+            for (int j = 0; j < NT; ++j) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x[j], acc[j][i], 0, 0, 0);
         }
+    };
+    load(0, f[0]);
+    load(1, f[1]);
+    for (int k = 0; k < ks; k += 2) {
+        step(k, f[0]);
+        load(k + 2, f[0]);
+        if (k + 1 < ks) step(k + 1, f[1]);
+        load(k + 3, f[1]);
+    }
+}
+template <int NT, int MT, int R>
+__device__ __forceinline__ void tile_product(f32x4 (&acc)[NT][MT], const uint16_t* act, const bf16x8 (&f)[NT][FUSE_KS],
+                                             int ks, int lane) {
+    switch (ks) {  // uniform
+        case 8: tile_product<NT, MT, R, 8>(acc, act, f, lane); break;
+        case 1: tile_product<NT, MT, R, 1>(acc, act, f, lane); break;
+        case 2: tile_product<NT, MT, R, 2>(acc, act, f, lane); break;
+        case 3: tile_product<NT, MT, R, 3>(acc, act, f, lane); break;
+        case 4: tile_product<NT, MT, R, 4>(acc, act, f, lane); break;
+        case 5: tile_product<NT, MT, R, 5>(acc, act, f, lane); break;
+        case 6: tile_product<NT, MT, R, 6>(acc, act, f, lane); break;
+        default: tile_product<NT, MT, R, 7>(acc, act, f, lane); break;
     }
 }
 
-__device__ __forceinline__ uint2 pack4(const uint16_t (&h)[4]) {
-    return uint2{(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
+// Stores a lane's NR consecutive rows of a fragment.
+template <int NR>
+__device__ __forceinline__ void store_rows(SIMINF_GLOBAL uint16_t* p, const uint16_t (&h)[NR]) {
+    if constexpr (NR == 4)
+        *(SIMINF_GLOBAL u32x2*)p = u32x2{(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
+    else if constexpr (NR == 2)
+        *(SIMINF_GLOBAL uint32_t*)p = (uint32_t)h[0] | (uint32_t)h[1] << 16;
+    else
+        *p = h[0];
 }
 
-// One workgroup of NW wavefronts takes 16 MT rows through the network; the
-// wavefronts share a layer's column tiles.  The next layer's weights are
-// loaded while the current layer's activations are computed.  TRAIN (MT = 1):
-// keeps what the backward pass needs, then the pinball loss and its gradient,
-// and the chain dZ_{l-1} = (dZ_l W_l) * GELU'(Z_{l-1}) down to the first layer.
-// Every product runs over its reduction in steps of 32 from the first, as in
-// gemm_kernel, so the results are the same bit for bit.
+// One workgroup of NW wavefronts takes MT tiles of R rows through the network; the
+// wavefronts share a layer's column tiles.  The next layer's bias and weights
+// are on their way while the current layer's activations are computed.  TRAIN
+// (MT = 1): keeps what the backward pass needs, then the pinball loss and its
+// gradient, and the chain dZ_{l-1} = (dZ_l W_l) * GELU'(Z_{l-1}) down to the
+// first layer.  Every product runs over its reduction in steps of 32 from the
+// first, as in gemm_kernel, so the results are the same bit for bit.
 //
 // What bounds it: small batches, the chain of layers (weights from L2, the
-// products, the activations, a barrier, about 2 us each); large ones, the
-// activations (about 58 instructions each, 67 million at batch 65,536, or 100
-// us of vector work).  Measured on 8 -> 256 x 4 -> 156, before (a product
-// kernel a layer and 42 launches a training step) and after: inference at
-// 65,536 rows 275 -> 144 us; 4 members at 1,000 rows 516 -> 21 us and at 8 rows
-// 296 -> 18 us with their combination; a gradient at 4,096 rows with its
-// read-back 800 -> 275 us; a training step at 128 rows 397 -> 50 us.
-template <int NW, int MT, bool TRAIN>
-__global__ void __launch_bounds__(NW * 64) fused_kernel(FusedArgs a) {
+// products, the activations, a barrier: about 2 us each); large ones, the
+// activations (about half of 65,536 rows' time) and the LDS reads of the
+// products.  Measured on 8 -> 256 x 4 -> 156, before (a product kernel a layer
+// and 42 launches a training step) and after: inference at 65,536 rows 275 ->
+// 99 us; 4 members at 1,000 rows with their combination 517 -> 19 us and at 8
+// rows 296 -> 16 us; a gradient at 4,096 rows with its read-back 804 -> 267 us;
+// a training step at 128 rows 395 -> 34 us.  On the way there, the kernel
+// alone: descriptor fields read from memory in every layer instead of the
+// arguments 35 us a training step against 32; the exact activations in place
+// of gelu_bf16, 16 rows a tile instead of 4 and weights loaded a layer ahead
+// for 64-row tiles (213 registers, one workgroup a CU) 144 us for 65,536 rows
+// against 111.
+template <int NW, int MT, int R, bool TRAIN>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) fused_kernel(FusedArgs a) {
     static_assert(!TRAIN || MT == 1, "training takes one row tile");
     constexpr int NT = FUSE_W / 16 / NW;
+    constexpr int NR = R / 4;  // rows a lane holds of a result tile
+    // with one row tile the next layer's weights are loaded ahead of the
+    // activations; with more, two workgroups a CU hide each other's loads
+    constexpr bool PRE = MT == 1;
     constexpr int BUFS = MT <= 2 ? 2 : 1;  // activations: in place needs a second barrier a layer
-    __shared__ __attribute__((aligned(16))) uint16_t act[BUFS][MT * 16 * ALD];
+    __shared__ __attribute__((aligned(16))) uint16_t act[BUFS][MT * R * ALD];
     __shared__ double red[NW];
-    const NetDesc& d = *a.net[blockIdx.y];
+    const NetArg& d = a.net[blockIdx.y];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int row0 = blockIdx.x * (MT * 16);
+    const int tile = blockIdx.x, row0 = tile * (MT * R);
     const int L = d.L, B = a.B;
-    const int cl = lane & 15, rq = (lane >> 4) * 4;  // the lane's column and first row of a result tile
-    // training: where the lane's four rows of a column tile go in a fragment
-    // of 32 rows (two row tiles share it)
-    const int tile = blockIdx.x;
-    const int frow = (tile & 1) * 16 + rq;
+    const int cl = lane & 15, rq = (lane >> 4) * NR;  // the lane's column and first row of a result tile
+    const SIMINF_GLOBAL bf16x8* wf = (const SIMINF_GLOBAL bf16x8*)d.Wf;
+    const SIMINF_GLOBAL float* pp = (const SIMINF_GLOBAL float*)d.p;
+    const SIMINF_GLOBAL float* X = (const SIMINF_GLOBAL float*)a.X;
+    SIMINF_GLOBAL uint16_t* Af = (SIMINF_GLOBAL uint16_t*)d.Af;
+    SIMINF_GLOBAL uint16_t* Df = (SIMINF_GLOBAL uint16_t*)d.Df;
+    SIMINF_GLOBAL float* zs = (SIMINF_GLOBAL float*)d.zs;
+    const size_t zstep = (size_t)d.rows32 * 32 * FUSE_W;
+    // training: where the lane's rows of a column tile go in a fragment of 32
+    // rows
+    const int step = row0 >> 5, frow = (row0 & 31) + rq;
     const int fpos = ((frow >> 3) * 16 + cl) * 8 + (frow & 7);
-    int cur = 0;
-    {
-        const int K = d.dims[0], kp = 32 * steps32(K);
-        for (int i = tid; i < MT * 16 * kp; i += NW * 64) {
-            const int r = i / kp, k = i % kp;
-            const uint16_t h = (row0 + r < B && k < K) ? f32_to_bf16(a.X[(size_t)(row0 + r) * K + k]) : (uint16_t)0;
-            act[0][r * ALD + k] = h;
-            if constexpr (TRAIN) {
-                const int b = (tile & 1) * 16 + r;
-                d.Af[0][((size_t)(tile >> 1) * (kp / 16) + (k >> 4)) * FRAG + ((b >> 3) * 16 + (k & 15)) * 8 + (b & 7)] = h;
-            }
-        }
-    }
-    bf16x8 f[NT][FUSE_W / 32];
-    int nt = 2 * steps32(d.dims[1]), ks = steps32(d.dims[0]);
-    load_frags<NT, NW>(f, d.Wf[0], nt, ks, wave, lane);
-    double part = 0.0;
-    for (int l = 0; l < L; ++l) {
-        const int N = d.dims[l + 1];
-        const float* bias = d.p + d.off[2 * l + 1];
-        float bn[NT];
+    int N = d.dims[1], nt = 2 * steps32(N), ks = steps32(d.dims[0]);
+    float bn[NT];
+    bf16x8 f[NT][FUSE_KS];
+    auto load_bias = [&](int n0) {
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
             const int n = (wave + j * NW) * 16 + cl;
-            bn[j] = n < N ? bias[n] : 0.f;
+            bn[j] = n < n0 ? pp[n] : 0.f;
         }
+    };
+    pp += N * d.dims[0];
+    load_bias(N);
+    if constexpr (PRE) load_frags<NT, NW>(f, wf, nt, ks, wave, lane);
+    float tv[NT][NR];  // training: the lane's targets
+    if constexpr (TRAIN) {
+        const SIMINF_GLOBAL float* T = (const SIMINF_GLOBAL float*)a.T;
+        const int No = d.dims[L];
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const int n = (wave + j * NW) * 16 + cl, b = row0 + rq + r;
+                tv[j][r] = b < B && n < No ? T[(size_t)b * No + n] : 0.f;
+            }
+    }
+    {
+        const int K = d.dims[0], kp = 32 * ks;
+        for (int i = tid; i < MT * R * kp; i += NW * 64) {
+            const int r = i / kp, k = i % kp;
+            const uint16_t h = (row0 + r < B && k < K) ? f32_to_bf16(X[(size_t)(row0 + r) * K + k]) : (uint16_t)0;
+            act[0][r * ALD + k] = h;
+            if constexpr (TRAIN) {
+                const int b = (row0 & 31) + r;
+                Af[((size_t)step * (kp / 16) + (k >> 4)) * FRAG + ((b >> 3) * 16 + (k & 15)) * 8 + (b & 7)] = h;
+            }
+        }
+        Af += (size_t)d.rows32 * (kp / 16) * FRAG;
+    }
+    int cur = 0;
+    double part = 0.0;
+    float zp[NT][NR];  // training: the pre-activations of the layer being differentiated
+    auto zat = [&](int t) { return (((size_t)tile * (FUSE_W / 16) + t) * 64 + lane) * NR; };
+    auto load_z = [&](int l, int n) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const SIMINF_GLOBAL float* q = zs + l * zstep + zat(min(wave + j * NW, n - 1));
+#pragma unroll
+            for (int r = 0; r < NR; ++r) zp[j][r] = q[r];
+        }
+    };
+    for (int l = 0; l < L; ++l) {
+        const bool last = l + 1 == L;
         __syncthreads();
         f32x4 acc[NT][MT];
-        tile_product<NT, MT, NW>(acc, act[cur], f, nt, ks, wave, lane);
-        const int ntc = nt;
-        if (l + 1 < L) {
-            nt = 2 * steps32(d.dims[l + 2]);
-            ks = steps32(N);
-            load_frags<NT, NW>(f, d.Wf[l + 1], nt, ks, wave, lane);
-        } else if (TRAIN && L > 1) {
-            nt = 2 * steps32(d.dims[L - 1]);
-            ks = steps32(N);
-            load_frags<NT, NW>(f, d.Wt[L - 1], nt, ks, wave, lane);
+        if constexpr (PRE) tile_product<NT, MT, R>(acc, act[cur], f, ks, lane);
+        else stream_product<NT, MT, NW>(acc, act[cur], wf, nt, ks, wave, lane);
+        float bc[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) bc[j] = bn[j];
+        const int Nc = N, ntc = nt;
+        if (!last) {
+            wf += nt * ks * 64;
+            pp += N;
+            N = d.dims[l + 2];
+            ks = steps32(Nc);
+            nt = 2 * steps32(N);
+            pp += N * Nc;
+            load_bias(N);
+            if constexpr (PRE) load_frags<NT, NW>(f, wf, nt, ks, wave, lane);
         }
         if constexpr (BUFS == 1) __syncthreads();
         else cur ^= 1;
@@ -456,27 +655,30 @@ __global__ void __launch_bounds__(NW * 64) fused_kernel(FusedArgs a) {
             if (t >= ntc) continue;
 #pragma unroll
             for (int i = 0; i < MT; ++i) {
-                float z[4];
+                if constexpr (MT > 1) __builtin_amdgcn_sched_barrier(0);
+                float z[NR];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) z[r] = acc[j][i][r] + bn[j];
-                if (l + 1 < L) {
-                    uint16_t h[4];
+                for (int r = 0; r < NR; ++r) z[r] = acc[j][i][r] + bc[j];
+                if (!last) {
+                    uint16_t h[NR];
+                    gelu_bf16(z, h);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        h[r] = f32_to_bf16(gelu(z[r]));
+                    for (int r = 0; r < NR; ++r) {
                         if (TRAIN && row0 + rq + r >= B) h[r] = 0;
-                        act[cur][(i * 16 + rq + r) * ALD + n] = h[r];
+                        act[cur][(i * R + rq + r) * ALD + n] = h[r];
                     }
                     if constexpr (TRAIN) {
-                        d.zs[l][((size_t)tile * (FUSE_W / 16) + t) * 64 + lane] = float4{z[0], z[1], z[2], z[3]};
-                        *reinterpret_cast<uint2*>(d.Af[l + 1] + ((size_t)(tile >> 1) * ntc + t) * FRAG + fpos) = pack4(h);
+                        
+#pragma unroll
+                        for (int r = 0; r < NR; ++r) zs[l * zstep + zat(t) + r] = z[r];
+                        store_rows(Af + ((size_t)step * ntc + t) * FRAG + fpos, h);
                     }
                 } else if constexpr (!TRAIN) {
-                    float* Y = a.Y ? a.Y : d.Y;
+                    SIMINF_GLOBAL float* Y = (SIMINF_GLOBAL float*)d.Y;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int b = row0 + i * 16 + rq + r;
-                        if (b < B && n < N) Y[(size_t)b * N + n] = z[r];
+                    for (int r = 0; r < NR; ++r) {
+                        const int b = row0 + i * R + rq + r;
+                        if (b < B && n < Nc) Y[(size_t)b * Nc + n] = z[r];
                     }
                 } else {
                     // pinball loss and its gradient dY / (B N)
@@ -484,53 +686,74 @@ __global__ void __launch_bounds__(NW * 64) fused_kernel(FusedArgs a) {
                     const int c = n % a.lv.nq;
 #pragma unroll
                     for (int e = 1; e < 8; ++e) q = c == e ? a.lv.q[e] : q;
-                    const float total = (float)(B * N);
-                    uint16_t h[4];
+                    const float total = (float)(B * Nc);
+                    uint16_t h[NR];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int b = row0 + rq + r;
+                    for (int r = 0; r < NR; ++r) {
                         h[r] = 0;
-                        if (b < B && n < N) {
-                            const float e = a.T[(size_t)b * N + n] - z[r];
+                        if (row0 + rq + r < B && n < Nc) {
+                            const float e = tv[j][r] - z[r];
                             part += e > 0.f ? (double)q * e : (double)(q - 1.f) * e;
                             h[r] = f32_to_bf16((e > 0.f ? -q : 1.f - q) / total);
                         }
                         act[cur][(rq + r) * ALD + n] = h[r];
                     }
-                    *reinterpret_cast<uint2*>(d.Df[l] + ((size_t)(tile >> 1) * ntc + t) * FRAG + fpos) = pack4(h);
+                    store_rows(Df + ((size_t)step * ntc + t) * FRAG + fpos, h);
                 }
+            }
+        }
+        if constexpr (TRAIN) {
+            if (!last) {
+                Af += (size_t)d.rows32 * ntc * FRAG;
+                Df += (size_t)d.rows32 * ntc * FRAG;
             }
         }
     }
     if constexpr (TRAIN) {
+        // the weights of layer l for the input gradient are as many fragments
+        // as for the forward product, at the same place in their array
+        const SIMINF_GLOBAL bf16x8* wt = (const SIMINF_GLOBAL bf16x8*)d.Wt + (wf - (const SIMINF_GLOBAL bf16x8*)d.Wf);
+        if (L > 1) {
+            ks = steps32(N);
+            nt = 2 * steps32(d.dims[L - 1]);
+            load_z(L - 2, nt);
+            load_frags<NT, NW>(f, wt, nt, ks, wave, lane);
+        }
         for (int l = L - 1; l > 0; --l) {
-            // dZ_l is in act[cur], Wt[l] in f: dZ_{l-1} of the columns K = dims[l]
-            float4 zp[NT];
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-                if (wave + j * NW < nt) zp[j] = d.zs[l - 1][((size_t)tile * (FUSE_W / 16) + wave + j * NW) * 64 + lane];
+            // dZ_l is in act[cur], Wt of layer l in f, Z_{l-1} in zp
             __syncthreads();
             f32x4 acc[NT][1];
-            tile_product<NT, 1, NW>(acc, act[cur], f, nt, ks, wave, lane);
+            tile_product<NT, 1, R>(acc, act[cur], f, ks, lane);
             const int ntc = nt;
+            float z[NT][NR];
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < NR; ++r) z[j][r] = zp[j][r];
+            Df -= (size_t)d.rows32 * ntc * FRAG;
             if (l > 1) {
-                nt = 2 * steps32(d.dims[l - 1]);
                 ks = steps32(d.dims[l]);
-                load_frags<NT, NW>(f, d.Wt[l - 1], nt, ks, wave, lane);
+                nt = 2 * steps32(d.dims[l - 1]);
+                wt -= nt * ks * 64;
+                load_z(l - 2, nt);
+                load_frags<NT, NW>(f, wt, nt, ks, wave, lane);
             }
             cur ^= 1;
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 const int t = wave + j * NW, n = t * 16 + cl;
                 if (t >= ntc) continue;
-                const float z[4] = {zp[j].x, zp[j].y, zp[j].z, zp[j].w};
-                uint16_t h[4];
+                float v[NR];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    h[r] = row0 + rq + r < B ? f32_to_bf16(acc[j][0][r] * gelu_grad(z[r])) : (uint16_t)0;
+                for (int r = 0; r < NR; ++r) v[r] = acc[j][0][r];
+                uint16_t h[NR];
+                gelu_grad_bf16(v, z[j], h);
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    if (row0 + rq + r >= B) h[r] = 0;
                     act[cur][(rq + r) * ALD + n] = h[r];
                 }
-                *reinterpret_cast<uint2*>(d.Df[l - 1] + ((size_t)(tile >> 1) * ntc + t) * FRAG + fpos) = pack4(h);
+                store_rows(Df + ((size_t)step * ntc + t) * FRAG + fpos, h);
             }
         }
         for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
@@ -550,21 +773,25 @@ __global__ void __launch_bounds__(NW * 64) fused_kernel(FusedArgs a) {
 // sums are added in order in LDS.  The bias gradient is one more product, with
 // ones, in the workgroups of the first columns.
 template <int WS>
-__global__ void __launch_bounds__(WS * 64) fused_grad_kernel(const NetDesc* net, int B) {
+__global__ void __launch_bounds__(WS * 64) fused_grad_kernel(NetArg d, float* grads, int B) {
     __shared__ f32x4 red[WS > 1 ? WS : 1][6][64];
-    const NetDesc& d = *net;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    int l = 0, w = blockIdx.x;
-    for (; l < d.L; ++l) {
-        const int c = steps32(d.dims[l + 1]) * steps32(d.dims[l]);
-        if (w < c) break;
-        w -= c;
+    const SIMINF_GLOBAL bf16x8* P = (const SIMINF_GLOBAL bf16x8*)d.Df;
+    const SIMINF_GLOBAL bf16x8* Q = (const SIMINF_GLOBAL bf16x8*)d.Af;
+    SIMINF_GLOBAL float* gW = (SIMINF_GLOBAL float*)grads;
+    int w = blockIdx.x, N = d.dims[1], K = d.dims[0];
+    for (int l = 0; w >= steps32(N) * steps32(K); ++l) {
+        w -= steps32(N) * steps32(K);
+        P += (size_t)d.rows32 * steps32(N) * 2 * 64;
+        Q += (size_t)d.rows32 * steps32(K) * 2 * 64;
+        gW += N * K + N;
+        K = N;
+        N = d.dims[l + 2];
     }
-    const int N = d.dims[l + 1], K = d.dims[l];
     const int sk = steps32(K), sn = steps32(N);
     const int tn = w / sk, tk = w % sk;
-    const bf16x8* P = reinterpret_cast<const bf16x8*>(d.Df[l]) + (size_t)tn * 2 * 64 + lane;
-    const bf16x8* Q = reinterpret_cast<const bf16x8*>(d.Af[l]) + (size_t)tk * 2 * 64 + lane;
+    P += tn * 2 * 64 + lane;
+    Q += tk * 2 * 64 + lane;
     const size_t pstep = (size_t)sn * 2 * 64, qstep = (size_t)sk * 2 * 64;
     f32x4 acc[6];
 #pragma unroll
@@ -573,16 +800,31 @@ __global__ void __launch_bounds__(WS * 64) fused_grad_kernel(const NetDesc* net,
 #pragma unroll
     for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
     const int steps = steps32(B);
-    for (int s = wave; s < steps; s += WS) {
-        const bf16x8 p0 = P[s * pstep], p1 = P[s * pstep + 64], q0 = Q[s * qstep], q1 = Q[s * qstep + 64];
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p0, q0, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p0, q1, acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p1, q0, acc[2], 0, 0, 0);
-        acc[3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p1, q1, acc[3], 0, 0, 0);
-        if (tk == 0) {
-            acc[4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p0, ones, acc[4], 0, 0, 0);
-            acc[5] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p1, ones, acc[5], 0, 0, 0);
-        }
+    // two steps' operands are on their way at a time (past the end: the last
+    // one again, not used)
+    bf16x8 o[2][4];
+    auto load = [&](int s, bf16x8 (&x)[4]) {
+        const int c = min(s, steps - 1);
+        x[0] = P[c * pstep];
+        x[1] = P[c * pstep + 64];
+        x[2] = Q[c * qstep];
+        x[3] = Q[c * qstep + 64];
+    };
+    auto step = [&](const bf16x8 (&x)[4]) {
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[0], x[2], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[0], x[3], acc[1], 0, 0, 0);
+        acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[1], x[2], acc[2], 0, 0, 0);
+        acc[3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[1], x[3], acc[3], 0, 0, 0);
+        acc[4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[0], ones, acc[4], 0, 0, 0);
+        acc[5] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[1], ones, acc[5], 0, 0, 0);
+    };
+    load(wave, o[0]);
+    load(wave + WS, o[1]);
+    for (int s = wave; s < steps; s += 2 * WS) {
+        step(o[0]);
+        load(s + 2 * WS, o[0]);
+        if (s + WS < steps) step(o[1]);
+        load(s + 3 * WS, o[1]);
     }
     if constexpr (WS > 1) {
 #pragma unroll
@@ -599,8 +841,7 @@ __global__ void __launch_bounds__(WS * 64) fused_grad_kernel(const NetDesc* net,
 #pragma unroll
         for (int i = 0; i < 6; ++i) acc[i] = red[0][i][lane];
     }
-    float* gW = d.g + d.off[2 * l];
-    float* gb = d.g + d.off[2 * l + 1];
+    SIMINF_GLOBAL float* gb = gW + N * K;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -610,57 +851,82 @@ __global__ void __launch_bounds__(WS * 64) fused_grad_kernel(const NetDesc* net,
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int k = tk * 32 + j * 16 + (lane & 15);
-                if (k < K) gW[(size_t)n * K + k] = acc[i * 2 + j][r];
+                if (k < K) gW[n * K + k] = acc[i * 2 + j][r];
             }
             if (tk == 0 && (lane & 15) == 0) gb[n] = acc[4 + i][r];
         }
 }
 
-// The bfloat16 copies of a weight (layer l, output n, input k).
-__device__ __forceinline__ void store_bf16(const NetDesc& d, int l, int n, int k, float w) {
+// What the parameter kernels need of a network, by value.
+struct ParamArg {
+    float *p, *g, *m, *v;          // W_0, b_0, W_1, b_1, ... and likewise
+    uint16_t *Wf, *Wt;             // small networks: the fused kernels' weights
+    uint16_t* Wb[MAX_LAYERS];      // others: row-major weights of each layer
+    int32_t L, small;
+    int32_t dims[MAX_LAYERS + 1];
+};
+
+// Layer l's part of the parameters and of the fragment arrays, and the
+// bfloat16 copies of its weight (n, k).
+struct LayerAt {
+    long long p, frag;
+    int l, N, K;
+};
+__device__ __forceinline__ void next_layer(const ParamArg& d, LayerAt& y) {
+    y.p += (long long)y.N * y.K + y.N;
+    y.frag += 2ll * steps32(y.N) * steps32(y.K) * FRAG;
+    y.K = y.N;
+    y.N = d.dims[++y.l + 1];
+}
+__device__ __forceinline__ void store_bf16(const ParamArg& d, const LayerAt& y, int n, int k, float w) {
     const uint16_t h = f32_to_bf16(w);
-    const int N = d.dims[l + 1], K = d.dims[l];
     if (d.small) {
-        d.Wf[l][frag_at(n, k, steps32(K))] = h;
-        d.Wt[l][frag_at(k, n, steps32(N))] = h;
+        d.Wf[y.frag + frag_at(n, k, steps32(y.K))] = h;
+        d.Wt[y.frag + frag_at(k, n, steps32(y.N))] = h;
     } else {
-        d.Wb[l][(size_t)n * K + k] = h;
+        d.Wb[y.l][(size_t)n * y.K + k] = h;
     }
 }
 
-// AdamW on the float32 master parameters of every layer at once; refreshes the
-// bfloat16 copies.
-__global__ void __launch_bounds__(256) adamw_kernel(const NetDesc* net, float lr, float b1, float b2, float eps,
-                                                    float wd, float c1, float c2) {
-    const NetDesc& d = *net;
-    const long long total = d.off[2 * d.L];
-    for (long long i = blockIdx.x * 256ll + threadIdx.x; i < total; i += gridDim.x * 256ll) {
-        const float gi = d.g[i];
-        const float mi = b1 * d.m[i] + (1.f - b1) * gi;
-        const float vi = b2 * d.v[i] + (1.f - b2) * gi * gi;
-        d.m[i] = mi;
-        d.v[i] = vi;
-        const float mh = mi / c1, vh = vi / c2;
-        const float p = d.p[i];
-        const float w = p - lr * (mh / (sqrtf(vh) + eps) + wd * p);
-        d.p[i] = w;
-        int l = 0;
-        while (l + 1 < d.L && i >= d.off[2 * l + 2]) ++l;
-        if (i < d.off[2 * l + 1]) {
-            const uint32_t e = (uint32_t)(i - d.off[2 * l]), K = (uint32_t)d.dims[l];
-            store_bf16(d, l, (int)(e / K), (int)(e % K), w);
-        }
+// AdamW on the float32 master parameters of every layer at once (a layer's
+// weights and bias from a workgroup of their own on); refreshes the bfloat16
+// copies.
+__global__ void __launch_bounds__(256) adamw_kernel(ParamArg d, float lr, float b1, float b2, float eps, float wd,
+                                                    float c1, float c2) {
+    LayerAt y{0, 0, 0, d.dims[1], d.dims[0]};
+    long long block = blockIdx.x;
+    for (;;) {
+        const long long blocks = ((long long)y.N * y.K + y.N + 255) / 256;
+        if (block < blocks) break;
+        block -= blocks;
+        next_layer(d, y);
+    }
+    const long long e = block * 256 + threadIdx.x, nw = (long long)y.N * y.K;
+    if (e >= nw + y.N) return;
+    const long long i = y.p + e;
+    const float gi = d.g[i];
+    const float mi = b1 * d.m[i] + (1.f - b1) * gi;
+    const float vi = b2 * d.v[i] + (1.f - b2) * gi * gi;
+    d.m[i] = mi;
+    d.v[i] = vi;
+    const float mh = mi / c1, vh = vi / c2;
+    const float p = d.p[i];
+    const float w = p - lr * (mh / (sqrtf(vh) + eps) + wd * p);
+    d.p[i] = w;
+    if (e < nw) {
+        const uint32_t n = (uint32_t)((unsigned long long)e / (uint32_t)y.K);
+        store_bf16(d, y, (int)n, (int)(e - (long long)n * y.K), w);
     }
 }
 
 // Refreshes the bfloat16 copies of layer l from its master weights.
-__global__ void __launch_bounds__(256) weight_copy_kernel(const NetDesc* net, int l) {
-    const NetDesc& d = *net;
-    const uint32_t K = (uint32_t)d.dims[l];
-    const float* W = d.p + d.off[2 * l];
-    const long long total = (long long)d.dims[l + 1] * K;
+__global__ void __launch_bounds__(256) weight_copy_kernel(ParamArg d, int l) {
+    LayerAt y{0, 0, 0, d.dims[1], d.dims[0]};
+    while (y.l < l) next_layer(d, y);
+    const float* W = d.p + y.p;
+    const long long total = (long long)y.N * y.K;
     for (long long i = blockIdx.x * 256ll + threadIdx.x; i < total; i += gridDim.x * 256ll)
-        store_bf16(d, l, (int)((uint64_t)i / K), (int)((uint64_t)i % K), W[i]);
+        store_bf16(d, y, (int)(i / y.K), (int)(i % y.K), W[i]);
 }
 
 __global__ void to_bf16_kernel(const float* x, uint16_t* y, long long n) {
@@ -762,11 +1028,10 @@ struct siminf_mlp {
     std::vector<void*> owned;
     std::vector<float*> W, b, gW, gb;  // into the parameter and gradient arrays
     std::vector<float*> Z;
-    std::vector<uint16_t*> Wb, A, dZ;  // general path
-    float *mom1 = nullptr, *mom2 = nullptr;
+    std::vector<uint16_t*> A, dZ;      // general path
     long long nparams = 0;
-    NetDesc host{};
-    NetDesc* desc = nullptr;           // the same in device memory
+    ParamArg par{};
+    NetArg net{};                      // small networks
     double* loss = nullptr;            // one sum a row tile (general path: one)
     std::vector<double> loss_host;     // read back by siminf_mlp_backward
     float* work = nullptr;   // general path: split-K partial products of the weight gradients
@@ -784,20 +1049,37 @@ bool dalloc(siminf_mlp* m, size_t n, T** p) {
     return hipMemset(*p, 0, sizeof(T) * std::max<size_t>(n, 1)) == hipSuccess;
 }
 
+// Rows of a workgroup's tile: the fewest of 4, 8 and 16 whose workgroups still
+// have a CU each, because a CU's time for a layer is mostly its rows'
+// activations.
+constexpr int FUSE_CUS = 256;
+int tile_rows(long long rows) { return rows <= 4 * FUSE_CUS ? 4 : rows <= 8 * FUSE_CUS ? 8 : 16; }
+
 // The fused forward pass of K networks (all small, of the same widths in and
-// out) on the same B rows; Y null: each into its own buffer.
+// out) on the same B rows into Y, or (Y null) each into its own buffer.
 hipError_t fused_forward(siminf_mlp* const* nets, int K, const float* X, int B, float* Y, hipStream_t st) {
-    FusedArgs a{};
-    for (int k = 0; k < K; ++k) a.net[k] = nets[k]->desc;
-    a.X = X;
-    a.Y = Y;
-    a.B = B;
-    const long long tiles = (long long)((B + 15) / 16) * K;
-    if (tiles <= 1024)
-        fused_kernel<16, 1, false><<<dim3((B + 15) / 16, K), 1024, 0, st>>>(a);
-    else
-        fused_kernel<8, 8, false><<<dim3((B + 127) / 128, K), 512, 0, st>>>(a);
-    return hipGetLastError();
+    for (int k0 = 0; k0 < K; k0 += FUSE_NETS) {
+        const int kn = std::min(FUSE_NETS, K - k0);
+        FusedArgs a{};
+        for (int k = 0; k < kn; ++k) {
+            a.net[k] = nets[k0 + k]->net;
+            if (Y) a.net[k].Y = Y;
+        }
+        a.X = X;
+        a.B = B;
+        if ((long long)((B + 15) / 16) * kn > 4 * FUSE_CUS) {
+            fused_kernel<8, 4, 16, false><<<dim3((B + 63) / 64, kn), 512, 0, st>>>(a);
+        } else {
+            const int R = tile_rows((long long)B * kn);
+            const dim3 grid((B + R - 1) / R, kn);
+            if (R == 4) fused_kernel<16, 1, 4, false><<<grid, 1024, 0, st>>>(a);
+            else if (R == 8) fused_kernel<16, 1, 8, false><<<grid, 1024, 0, st>>>(a);
+            else fused_kernel<16, 1, 16, false><<<grid, 1024, 0, st>>>(a);
+        }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // train: keep the float32 pre-activations that the backward pass needs.
@@ -812,7 +1094,7 @@ int mlp_forward(siminf_mlp* m, const float* X, int B, hipStream_t st, bool train
         g.K = m->dims[l];
         g.A = m->A[l];
         g.lda = m->dims[l];
-        g.B = m->Wb[l];
+        g.B = m->par.Wb[l];
         g.ldb = m->dims[l];
         g.bias = m->b[l];
         g.Cf = m->Z[l];
@@ -843,7 +1125,7 @@ int ensemble_predict(siminf_mlp* const* nets, int K, const float* X, int B, cons
     for (int k = 0; k < K; ++k) {
         slice = std::min(slice, nets[k]->max_batch);
         if (nets[k]->small) fused[nf++] = nets[k];
-        o.P[k] = nets[k]->small ? nets[k]->host.Y : nets[k]->Z[nets[k]->L - 1];
+        o.P[k] = nets[k]->small ? nets[k]->net.Y : nets[k]->Z[nets[k]->L - 1];
     }
     for (int b0 = 0; b0 < B; b0 += slice) {
         const int bs = std::min(slice, B - b0);
@@ -891,59 +1173,61 @@ int siminf_mlp_create(int32_t nlayers, const int32_t* dims, int32_t max_batch, s
     m->gW.resize(nlayers);
     m->gb.resize(nlayers);
     m->Z.resize(nlayers);
-    m->Wb.resize(nlayers);
     m->dZ.resize(nlayers);
     m->A.resize(nlayers);
-    NetDesc& d = m->host;
+    ParamArg& d = m->par;
+    NetArg& na = m->net;
     d.L = nlayers;
-    size_t wmax = 1, nmax = 1;
+    const size_t rows = (size_t)max_batch, sb = (size_t)steps32(max_batch);
+    size_t wmax = 1, nmax = 1, wfrags = 0, afrags = 0, dfrags = 0;
     int widest = 1;
     for (int l = 0; l <= nlayers; ++l) {
         d.dims[l] = dims[l];
         widest = std::max(widest, dims[l]);
     }
     for (int l = 0; l < nlayers; ++l) {
-        const size_t nw = (size_t)dims[l + 1] * dims[l];
-        d.off[2 * l] = m->nparams;
-        d.off[2 * l + 1] = m->nparams + (long long)nw;
-        m->nparams += (long long)nw + dims[l + 1];
-        wmax = std::max(wmax, nw);
-        nmax = std::max(nmax, (size_t)dims[l + 1]);
+        const size_t N = dims[l + 1], K = dims[l];
+        m->nparams += (long long)(N * K + N);
+        wfrags += (size_t)2 * steps32(N) * steps32(K);
+        afrags += 2 * sb * steps32(K);
+        dfrags += 2 * sb * steps32(N);
+        wmax = std::max(wmax, N * K);
+        nmax = std::max(nmax, N);
     }
-    d.off[2 * nlayers] = m->nparams;
     // the fused kernels hold a row tile's activations in LDS and a layer's
     // share of weights in registers; they apply to every batch size
-    m->small = widest <= FUSE_W;
+    m->small = widest <= FUSE_W && nlayers <= FUSE_L;
     d.small = m->small ? 1 : 0;
-    const size_t np = (size_t)m->nparams, rows = (size_t)max_batch;
+    const size_t np = (size_t)m->nparams;
     bool ok = dalloc(m, np, &d.p) && dalloc(m, np, &d.g) && dalloc(m, np, &d.m) && dalloc(m, np, &d.v);
-    m->mom1 = d.m;
-    m->mom2 = d.v;
+    long long at = 0;
     for (int l = 0; ok && l < nlayers; ++l) {
-        m->W[l] = d.p + d.off[2 * l];
-        m->b[l] = d.p + d.off[2 * l + 1];
-        m->gW[l] = d.g + d.off[2 * l];
-        m->gb[l] = d.g + d.off[2 * l + 1];
         const size_t N = dims[l + 1], K = dims[l];
-        if (m->small) {
-            const size_t sn = steps32(N), sk = steps32(K), sb = steps32(max_batch);
-            ok = dalloc(m, 2 * sn * sk * FRAG, &d.Wf[l]) && dalloc(m, 2 * sn * sk * FRAG, &d.Wt[l]) &&
-                 dalloc(m, 2 * sb * sk * FRAG, &d.Af[l]) && dalloc(m, 2 * sb * sn * FRAG, &d.Df[l]) &&
-                 (l + 1 == nlayers || dalloc(m, 2 * sb * (FUSE_W / 16) * 64, &d.zs[l]));
-        } else {
-            ok = dalloc(m, rows * N, &m->Z[l]) && dalloc(m, N * K, &m->Wb[l]) && dalloc(m, rows * N, &m->dZ[l]) &&
+        m->W[l] = d.p + at;
+        m->gW[l] = d.g + at;
+        m->b[l] = m->W[l] + N * K;
+        m->gb[l] = m->gW[l] + N * K;
+        at += (long long)(N * K + N);
+        if (!m->small)
+            ok = dalloc(m, rows * N, &m->Z[l]) && dalloc(m, N * K, &d.Wb[l]) && dalloc(m, rows * N, &m->dZ[l]) &&
                  dalloc(m, rows * K, &m->A[l]);
-            d.Wb[l] = m->Wb[l];
-        }
     }
     if (m->small) {
-        ok = ok && dalloc(m, rows * dims[nlayers], &d.Y) && dalloc(m, 2 * (size_t)steps32(max_batch), &m->loss);
+        ok = ok && dalloc(m, wfrags * FRAG, &d.Wf) && dalloc(m, wfrags * FRAG, &d.Wt) &&
+             dalloc(m, afrags * FRAG, &na.Af) && dalloc(m, dfrags * FRAG, &na.Df) &&
+             dalloc(m, (size_t)(nlayers - 1) * sb * 32 * FUSE_W, &na.zs) &&
+             dalloc(m, rows * dims[nlayers], &na.Y) && dalloc(m, 8 * sb, &m->loss);
+        na.Wf = d.Wf;
+        na.Wt = d.Wt;
+        na.p = d.p;
+        na.L = nlayers;
+        na.rows32 = (int32_t)sb;
+        for (int l = 0; l <= nlayers; ++l) na.dims[l] = dims[l];
     } else {
         ok = ok && dalloc(m, 1, &m->loss) && dalloc(m, (size_t)MAX_SLICES * wmax, &m->work) &&
              dalloc(m, (rows + 255) / 256 * nmax, &m->cpart);
     }
-    m->loss_host.assign(m->small ? 2 * (size_t)steps32(max_batch) : 1, 0.0);
-    ok = ok && dalloc(m, 1, &m->desc) && hipMemcpy(m->desc, &d, sizeof(NetDesc), hipMemcpyHostToDevice) == hipSuccess;
+    m->loss_host.assign(m->small ? 8 * sb : 1, 0.0);
     if (!ok) return SIMINF_E_ALLOC;
     return SIMINF_OK;
 }
@@ -951,14 +1235,14 @@ int siminf_mlp_create(int32_t nlayers, const int32_t* dims, int32_t max_batch, s
 int siminf_mlp_set_params(siminf_mlp* m, int32_t layer, const float* W, const float* b) {
     if (!m || layer < 0 || layer >= m->L || !W || !b) return SIMINF_E_ARG;
     const size_t nw = (size_t)m->dims[layer + 1] * m->dims[layer], nb = m->dims[layer + 1];
-    const long long at = m->host.off[2 * layer];
+    const ptrdiff_t at = m->W[layer] - m->par.p;
     // the layer's weights and bias are neighbours in every array
     if (hipMemcpy(m->W[layer], W, nw * 4, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(m->b[layer], b, nb * 4, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemset(m->mom1 + at, 0, (nw + nb) * 4) != hipSuccess ||
-        hipMemset(m->mom2 + at, 0, (nw + nb) * 4) != hipSuccess)
+        hipMemset(m->par.m + at, 0, (nw + nb) * 4) != hipSuccess ||
+        hipMemset(m->par.v + at, 0, (nw + nb) * 4) != hipSuccess)
         return SIMINF_E_DEVICE;
-    weight_copy_kernel<<<grid_for((long long)nw), 256, 0, nullptr>>>(m->desc, layer);
+    weight_copy_kernel<<<grid_for((long long)nw), 256, 0, nullptr>>>(m->par, layer);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) return SIMINF_E_DEVICE;
     m->t = 0;
     return SIMINF_OK;
@@ -1007,22 +1291,25 @@ int siminf_mlp_backward(siminf_mlp* m, const float* X, const float* T, int32_t B
         // a launch for the rows' forward and backward chain, one for the
         // gradients' reductions over the batch
         FusedArgs a{};
-        a.net[0] = m->desc;
+        a.net[0] = m->net;
         a.X = X;
         a.T = T;
         a.loss = m->loss;
         a.lv = lv;
         a.B = B;
-        sums = 2 * steps32(B);
-        fused_kernel<16, 1, true><<<sums, 1024, 0, st>>>(a);
+        const int R = tile_rows(B);
+        sums = 32 / R * steps32(B);
+        if (R == 4) fused_kernel<16, 1, 4, true><<<sums, 1024, 0, st>>>(a);
+        else if (R == 8) fused_kernel<16, 1, 8, true><<<sums, 1024, 0, st>>>(a);
+        else fused_kernel<16, 1, 16, true><<<sums, 1024, 0, st>>>(a);
         int tiles = 0;
         for (int l = 0; l < L; ++l) tiles += steps32(m->dims[l + 1]) * steps32(m->dims[l]);
         if (B <= 256)
-            fused_grad_kernel<1><<<tiles, 64, 0, st>>>(m->desc, B);
+            fused_grad_kernel<1><<<tiles, 64, 0, st>>>(m->net, m->par.g, B);
         else if (B <= 1024)
-            fused_grad_kernel<4><<<tiles, 256, 0, st>>>(m->desc, B);
+            fused_grad_kernel<4><<<tiles, 256, 0, st>>>(m->net, m->par.g, B);
         else
-            fused_grad_kernel<8><<<tiles, 512, 0, st>>>(m->desc, B);
+            fused_grad_kernel<8><<<tiles, 512, 0, st>>>(m->net, m->par.g, B);
         if (hipGetLastError() != hipSuccess) return SIMINF_E_DEVICE;
     } else {
         zero_kernel<<<1, 1, 0, st>>>(m->loss);
@@ -1057,7 +1344,7 @@ int siminf_mlp_backward(siminf_mlp* m, const float* X, const float* T, int32_t B
                 d.K = N;
                 d.A = m->dZ[l];
                 d.lda = N;
-                d.B = m->Wb[l];
+                d.B = m->par.Wb[l];
                 d.ldb = K;
                 d.Cb = m->dZ[l - 1];
                 d.ldcb = K;
@@ -1085,7 +1372,9 @@ int siminf_mlp_adamw(siminf_mlp* m, float lr, float beta1, float beta2, float ep
     hipStream_t st = (hipStream_t)hip_stream;
     m->t += 1;
     const float c1 = 1.f - powf(beta1, (float)m->t), c2 = 1.f - powf(beta2, (float)m->t);
-    adamw_kernel<<<grid_for(m->nparams), 256, 0, st>>>(m->desc, lr, beta1, beta2, eps, weight_decay, c1, c2);
+    long long blocks = 0;
+    for (int l = 0; l < m->L; ++l) blocks += ((long long)m->dims[l + 1] * (m->dims[l] + 1) + 255) / 256;
+    adamw_kernel<<<(unsigned)blocks, 256, 0, st>>>(m->par, lr, beta1, beta2, eps, weight_decay, c1, c2);
     return hipGetLastError() == hipSuccess ? SIMINF_OK : SIMINF_E_DEVICE;
 }
 

@@ -96,3 +96,39 @@ def test_ensemble_of_networks_in_slices(lib, widths):
     assert torch.allclose(dis.double(), P.std(0, unbiased=True).mean(1), rtol=1e-6, atol=0)
     for net in nets:
         net.close()
+
+
+@pytest.mark.parametrize("B", [3, 200, 700, 1500, 9000])
+@pytest.mark.parametrize("spread", [0.02, 1.0, 12.0])
+def test_fused_and_general_kernels_agree_bit_for_bit(lib, B, spread):
+    """The fused kernels settle most activations from a cheap GELU, the
+    general ones evaluate it.  A network one unit too wide for the fused
+    kernels whose extra units have zero weights is the same function, with the
+    same products in the same order: outputs must be equal bit for bit, and
+    so must the weight gradients of batches that both reduce in one pass,
+    for pre-activations from tiny to far beyond the cheap range, and zero."""
+    import torch
+    rng = np.random.default_rng(31)
+    widths = (8, 256, 256, 40)
+    params = [(spread * Wl, spread * rng.normal(scale=0.3, size=b.shape)) for Wl, b in W.mlp_init(widths, 9)]
+    wide = []
+    for l, (Wl, b) in enumerate(params):
+        out, inp = Wl.shape
+        Wx = np.zeros((out + (l < 2), inp + (l > 0)))
+        Wx[:out, :inp] = Wl
+        wide.append((Wx, np.append(b, 0.0) if l < 2 else b))
+    X = rng.normal(size=(B, 8)).astype(np.float32)
+    X[rng.random((B, 8)) < 0.1] = 0.0
+    Xt = torch.from_numpy(X).cuda()
+    T = torch.from_numpy(rng.normal(size=(B, 40)).astype(np.float32)).cuda()
+    a, g = lib.MLP(widths, B), lib.MLP((8, 257, 257, 40), B)
+    a.set_params(params)
+    g.set_params(wide)
+    assert torch.equal(a.forward(Xt), g.forward(Xt))
+    la, lg = a.backward(Xt, T, PROBS), g.backward(Xt, T, PROBS)
+    assert abs(la - lg) <= 1e-12 * abs(lg)
+    if B <= 256:
+        for (Wa, _), (Wg, _) in zip(a.get_grads(), g.get_grads()):
+            assert np.array_equal(Wa, Wg[:Wa.shape[0], :Wa.shape[1]])
+    a.close()
+    g.close()
