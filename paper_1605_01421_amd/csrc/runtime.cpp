@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <numeric>
 #include <string>
 #include <tuple>
@@ -259,6 +260,48 @@ int default_group(const Group& g, int nbig, int div) {
     return (g.n - nbig + div - 1) / div;
 }
 
+// The launch shape of a handle whose options fix none (windows of steps apply,
+// no lane queue): *nbig nodes on a wavefront each, *ngrp on a group of lanes.
+// A day costs a wavefront about one window for every 64 draws of a wide node
+// or 8 of a grouped one, and the days of a run are a chain, so lanes that are
+// to spare are spent on windows; but wavefronts that share a SIMD slow each
+// other down, so the wide nodes are the heaviest, two a CU, of those above twice
+// the mean work, and more only while a SIMD has no second wavefront (nodes of
+// over 250 individuals: a few windows a day on a group), unless every node
+// qualifies and there is room for all.  SIR with events over 200 days, ms (the
+// wide nodes of the work cut and no groups; two a CU and every other node on a
+// group): 10,000 nodes 2.20 -> 1.09 (1.16 with 128 wide, 1.18 with 1,200);
+// 2,500 nodes 1.39 -> 0.78; 10,000 nodes without events 1.63 -> 0.79.  2,000
+// equal nodes: all wide 0.50, 512 wide 0.56.  More nodes than groups can hold:
+// the heaviest tenth on groups, the rest on lanes (SISe, 37,000 nodes: 1.93 ->
+// 1.43, and 1.55 with a quarter on groups and 64 nodes a wavefront).
+void default_shape(const Group& g, int cus, int* nbig, int* ngrp, int* pack) {
+    if (*nbig < g.n || g.n > 8 * cus) {
+        double total = 0;
+        for (int64_t w : g.work) total += (double)w;
+        // as many as leave one wavefront a SIMD with the others on groups
+        const int room = (4 * cus * 8 - g.n) / 7;
+        int nb = 0;
+        while (nb < std::min(g.n, 2 * cus) && (double)g.work[nb] * g.n > 2.0 * total) ++nb;
+        while (nb < std::min(g.n, room) && g.work[nb] > 250) ++nb;
+        *nbig = nb;
+    }
+    const int rest = g.n - *nbig;
+    // resident wavefronts: three a SIMD in the kernels with groups
+    const bool resident = g.n_e2 > 0;
+    const long long waves = *nbig + (rest + WAVE / GROUP_LANES - 1) / (WAVE / GROUP_LANES);
+    const bool all = !resident || waves <= 12ll * cus;
+    *ngrp = all ? rest : rest / 10;
+    if (!all) *pack = -16;
+}
+
+// Fewest nodes that the lane queue is chosen for by itself: one a lane of the
+// device at its lowest occupancy, and three where the lockstep kernel can give
+// every node a group of lanes instead (SIR and SISe sets together: 58,000
+// nodes 7.0 ms on the queue and 4.6 on groups, 326,000 23.2 and 20.4, 469,000
+// 21.5 and 24.6).
+int64_t lane_queue_nodes(const KParams& p, int cus) { return (int64_t)(p.lattice ? 3 : 1) * cus * 4 * WAVE; }
+
 // Nodes of a lane-queue group too heavy for one lane, heaviest first: each gets
 // a whole wavefront, and the lanes keep the others.  A lane makes a step in
 // about 1.4 us when the SIMDs are full, so the heaviest node that stays on a
@@ -411,8 +454,11 @@ int configure(siminf_model* m, Group& g, int block, int nbig, int pipeline, int 
     // wavefront; then the largest packing that gives every SIMD one (at least
     // 16 nodes to a wavefront in the coupled kernel, whose posts every
     // wavefront polls), else the smallest allowed
-    const bool auto_pack = pack == 0;
-    if (auto_pack) {
+    // (pack < 0: -pack, raised like an automatic one where it does not fit)
+    const bool auto_pack = pack <= 0;
+    if (pack < 0) {
+        pack = -pack;
+    } else if (auto_pack) {
         const long long major = (long long)nbig + (ngrp + per_grp - 1) / per_grp;
         const long long rest = n - nbig - ngrp;
         pack = WAVE;
@@ -736,6 +782,18 @@ int create_impl(const siminf_spec* specs, int nspecs, const int32_t* reps, const
             for (int r : runs_sorted) {
                 const int si = m->runs[r].spec;
                 for (int32_t i : spec_order[si]) nodes.push_back({r, i, spec_work[si][i]});
+            }
+            // the lockstep kernel gives its first nodes a wavefront each: the
+            // heaviest of all runs then come first (two a CU)
+            const size_t top_n = (size_t)2 * cus;
+            if (nodes.size() > top_n && (int64_t)nodes.size() < (int64_t)3 * cus * 4 * WAVE) {
+                std::vector<int64_t> w;
+                for (const NodeRef& x : nodes) w.push_back(x.work);
+                std::nth_element(w.begin(), w.begin() + (ptrdiff_t)top_n, w.end(), std::greater<int64_t>());
+                const int64_t cut = w[top_n];
+                auto mid = std::stable_partition(nodes.begin(), nodes.end(),
+                                                 [&](const NodeRef& x) { return x.work > cut; });
+                std::stable_sort(nodes.begin(), mid, [](const NodeRef& x, const NodeRef& y) { return x.work > y.work; });
             }
         } else {
             for (int r : grp_runs) {
@@ -1073,30 +1131,27 @@ int create_impl(const siminf_spec* specs, int nspecs, const int32_t* reps, const
         }
         g.node_run = node_run;
         int lq = 0;
+        const bool shaped = m->opt.lanes != 0 || m->opt.wide != 0 || m->opt.group != 0 || m->opt.pack != 0;
         if (g.n_e2 == 0 && !coupled && !is_generated(g.model) && m->opt.solver == 0) {
             // the lane-queue chunk table: at most one chunk per run and per 64 nodes more
             g.chunk_cap = (int)grp_runs.size() + n / 64 + 1;
             if (alloc_device(m->owned, (size_t)g.chunk_cap, &g.d_chunks)) return hip_fail(m);
             const int chunk = m->opt.chunk > 0 ? m->opt.chunk : 512;
-            const bool shaped = m->opt.lanes != 0 || m->opt.wide != 0 || m->opt.group != 0 || m->opt.pack != 0;
             const int wpb = (m->opt.block ? m->opt.block : 256) / WAVE;
             if (m->opt.lane_queue == 1)
                 lq = chunk;
-            else if (m->opt.lane_queue == 0 && !shaped &&
-                     // (sums: with its heavy nodes on wavefronts the queue was
-                     // the faster kernel from 565 nodes, 2.1 against 7.6 ms, to
-                     // 84,000, 22 against 62 ms; full records of fewer nodes
-                     // are written better by the lockstep kernel)
-                     (m->record == SIMINF_RECORD_SUMS || (int64_t)n >= (int64_t)cus * 4 * WAVE) &&
+            else if (m->opt.lane_queue == 0 && !shaped && (int64_t)n >= lane_queue_nodes(p, cus) &&
                      lane_queue_lds(m, g, wpb) <= (size_t)LQ_LDS_BYTES)
                 lq = chunk;
         } else if (m->opt.lane_queue == 1) {
             set_create_error(m, SIMINF_E_UNSUPPORTED, -1, -1);
             return SIMINF_E_UNSUPPORTED;
         }
-        const int nb = default_wide(m, g);
-        const int rc = configure(m, g, m->opt.block, nb, m->opt.pipeline, m->opt.mode, m->opt.pack,
-                                 m->opt.group < 0 ? g.n : m->opt.group, lq, m->opt.batch ? m->opt.batch : 16);
+        int nb = default_wide(m, g), ng = m->opt.group < 0 ? g.n : m->opt.group, pack = m->opt.pack;
+        if (!shaped && m->opt.order == 0 && lq == 0 && p.lattice && p.solver == 0 && !coupled)
+            default_shape(g, cus, &nb, &ng, &pack);
+        const int rc = configure(m, g, m->opt.block, nb, m->opt.pipeline, m->opt.mode, pack, ng, lq,
+                                 m->opt.batch ? m->opt.batch : 16);
         if (rc) {
             set_create_error(m, rc, -1, -1);
             return rc;
