@@ -238,8 +238,8 @@ typedef struct {
                           32, 16, 8 or 4 (the remaining lanes idle); 0 auto: 64,
                           unless the device has more CUs than wavefronts, then
                           the largest packing that gives each SIMD a wavefront
-                          (at least 16 with SISe_sp coupling; 4 if none does),
-                          raised again where the dataflow kernel cannot hold
+                          (4 if none does; with SISe_sp coupling at least 16
+                          where lanes, wide or group is set), raised again where the dataflow kernel cannot hold
                           every wavefront.  Fewer
                           nodes per wavefront shorten a latency-bound run (each
                           wavefront's day ends with its slowest node, and an

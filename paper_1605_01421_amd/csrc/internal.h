@@ -106,15 +106,15 @@ __host__ __device__ inline int xcd_block(int b, int b0, int nblk, int g) {
 
 // What a node of a spatially coupled model posts for its neighbours each
 // day: its continuous state before the post-time step and its size after
-// the day's events; `day` (the day step, -1 before the run) is stored last
-// with release order and tells a reader the post is complete.  Two posts per
-// node (day parity): a node posts day b + 2 only after reading every
-// neighbour's day b + 1 post, which each neighbour makes only after reading
-// this node's day b post.
-struct CplPost {
-    double phi;
-    int32_t n;
-    int32_t day;
+// the day's events.  Every 8-byte word carries the day step in its high half
+// (-1 before the run) and 32 bits of the post in its low half, so a reader
+// sees from each word itself whether it is the day's: the words are stored and
+// loaded one by one without any order between them, and no fence writes back
+// or drops a cache.  Two posts per node (day parity): a node posts day b + 2
+// only after reading every neighbour's day b + 1 post, which each neighbour
+// makes only after reading this node's day b post.
+struct alignas(32) CplPost {
+    unsigned long long w[4];  // phi's low half, phi's high half, n; one unused
 };
 
 struct KParams {

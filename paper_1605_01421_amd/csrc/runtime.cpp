@@ -452,8 +452,7 @@ int configure(siminf_model* m, Group& g, int block, int nbig, int pipeline, int 
     ngrp = p.lattice ? std::max(0, std::min(ngrp, n - nbig)) : 0;
     // pack 0 (auto): 64 nodes to a wavefront, unless that leaves CUs without a
     // wavefront; then the largest packing that gives every SIMD one (at least
-    // 16 nodes to a wavefront in the coupled kernel, whose posts every
-    // wavefront polls), else the smallest allowed
+    // 16 nodes to a wavefront in the coupled kernel), else the smallest allowed
     // (pack < 0: -pack, raised like an automatic one where it does not fit)
     const bool auto_pack = pack <= 0;
     if (pack < 0) {
@@ -1150,6 +1149,17 @@ int create_impl(const siminf_spec* specs, int nspecs, const int32_t* reps, const
         int nb = default_wide(m, g), ng = m->opt.group < 0 ? g.n : m->opt.group, pack = m->opt.pack;
         if (!shaped && m->opt.order == 0 && lq == 0 && p.lattice && p.solver == 0 && !coupled)
             default_shape(g, cus, &nb, &ng, &pack);
+        // coupled nodes: a day is a round trip between neighbours and few draws,
+        // which windows do not shorten, and a wide node's 64 lanes take longer
+        // over its neighbours' terms (1,600 farms over 200 days: 1.61 ms with up
+        // to 128 wide nodes, 2.98 ms with 481, 1.98 ms with every node on a group);
+        // the lanes without a node read for the others, so few nodes a
+        // wavefront are best (2.03, 1.72 and 1.61 ms with 16, 8 and 4)
+        if (coupled && !shaped) {
+            nb = std::min(nb, cus / 8);
+            pack = -WAVE;
+            while (pack < -4 && nb + (n - nb - pack - 1) / -pack < 4 * cus) pack /= 2;
+        }
         const int rc = configure(m, g, m->opt.block, nb, m->opt.pipeline, m->opt.mode, pack, ng, lq,
                                  m->opt.batch ? m->opt.batch : 16);
         if (rc) {

@@ -695,6 +695,53 @@ __device__ __forceinline__ void record(const KParams& p, const Node<M>& s, int k
     }
 }
 
+// Where a lane that writes full records puts the next one of its node: the
+// records of a node are a fixed distance apart, so the places follow from one
+// another by additions.
+template <class M>
+struct RecordAt {
+    int32_t* u = nullptr;
+    double* v = nullptr;
+    size_t comp = 0;  // distance of a node's compartments in a record (rec_index)
+    size_t rec = 0;   // and of its records, in units of one compartment
+    int next = 0;     // index of the next record
+};
+
+template <class M>
+__device__ __forceinline__ RecordAt<M> record_at(const KParams& p, int k, int m) {
+    RecordAt<M> r;
+    r.next = m;
+    if (p.record == 0) {
+        r.comp = k < p.nmajor ? 1 : (size_t)(p.n - p.nmajor);
+        r.rec = r.comp;
+        r.u = p.U + rec_index(m, 0, k, M::NC, p.ntspan, p.n, p.nmajor);
+        if constexpr (M::NV > 0) r.v = p.V + rec_index(m, 0, k, M::NV, p.ntspan, p.n, p.nmajor);
+    }
+    return r;
+}
+
+// Writes the records up to tspan index m1 (exclusive).  All lanes of the wave
+// call this together; lanes that are not active contribute nothing.
+template <class M>
+__device__ __forceinline__ void record_to(const KParams& p, const Node<M>& s, RecordAt<M>& at, int k, int run,
+                                          bool active, int m1) {
+    if (p.record == 0) {
+        for (; at.next < m1; ++at.next) {
+            if (active) {
+#pragma unroll
+                for (int c = 0; c < M::NC; ++c) at.u[c * at.comp] = s.u[c];
+#pragma unroll
+                for (int c = 0; c < M::NV; ++c) at.v[c * at.comp] = s.v[c];
+            }
+            at.u += M::NC * at.rec;
+            if constexpr (M::NV > 0) at.v += M::NV * at.rec;
+        }
+    } else if (at.next < m1) {
+        record<M>(p, s, k, run, active, at.next, m1);
+        at.next = m1;
+    }
+}
+
 __device__ __forceinline__ void add_counters(Ctrl* c, unsigned long long tr, unsigned long long nd,
                                              unsigned long long ev, unsigned long long dr) {
     tr = wave_sum(tr);
@@ -1008,6 +1055,7 @@ __global__ void __launch_bounds__(256) free_kernel(KParams pa) {
 
         bool dead = false;
         uint64_t key_raw = 0;  // error key, refreshed every 8 days and read 8 days later
+        RecordAt<M> at = record_at<M>(p, k, p.rec_off[0]);
         for (int b = 0; b < p.nb; ++b) {
             if ((b & 7) == 0) {
                 if (b > 0 && (__shfl(key_raw, 0, WAVE) >> 44) < (uint64_t)b) break;
@@ -1015,6 +1063,7 @@ __global__ void __launch_bounds__(256) free_kernel(KParams pa) {
                     key_raw = __hip_atomic_load(&p.ctrl->err_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             const int64_t day = p.T1 + b;
+            const int rec_end = p.rec_off[b + 1];  // (read ahead of the day)
             if (grp) group_day<M>(p, s, active && !dead, b, day, node, stream, ord, cur, cend, nrec, dead, t, owner);
             if (active && !dead) {
                 if (!grp)
@@ -1025,7 +1074,7 @@ __global__ void __launch_bounds__(256) free_kernel(KParams pa) {
                 }
                 t.nd += owner ? 1 : 0;
             }
-            record<M>(p, s, k, run, owner, p.rec_off[b], p.rec_off[b + 1]);
+            record_to<M>(p, s, at, k, run, owner, rec_end);
         }
     }
     add_counters(p.ctrl, t.tr, t.nd, t.ev, t.dr);
@@ -1475,75 +1524,160 @@ __device__ __forceinline__ void take_mail(const KParams& p, int e, unsigned long
 
 // The coupling sum of a spatially coupled post-time step (SISe_sp): every
 // node posts its continuous state before the step and its size after the
-// day's events, waits for the day's posts of its neighbours, then adds up
-// their coupling terms in stored order.  Every node posts before it waits,
-// so every wait ends (all node wavefronts are resident in this kernel).
-// Posts alternate between two buffers by day parity.  A node also waits for
-// the day's posts of the nodes that read it (whether or not it reads them,
-// and whatever its size): it can then overwrite a buffer two days on only
-// after every reader has posted the next day, that is, has finished reading
-// the post it overwrites.  The wait looks at CPL_PEEK posts at once, so that
-// their round trips to memory overlap; one acquire fence then covers every
-// post read.
-// Called by every lane of the wavefront (the wait loop is wave-uniform);
-// `active` lanes carry a node, `owner` is the lane that posts for it, and
-// nodes that an error stopped keep posting their last state.  c is 0 for an
-// empty node.  A wait longer than the wall-clock limit abandons the run; an
-// earlier error lets the waits give up (the run's later results are
-// undefined).
-constexpr int CPL_PEEK = 8;
+// day's events, waits for the day's posts of its neighbours, and adds up
+// their coupling terms in stored order.  Every node posts before it waits, so
+// every wait ends (all node wavefronts are resident in this kernel).  Posts
+// alternate between two buffers by day parity.  A node also waits for the
+// day's posts of the nodes that read it (whether or not it reads them, and
+// whatever its size): it can then overwrite a buffer two days on only after
+// every reader has posted the next day, that is, has finished reading the post
+// it overwrites.
+//
+// A wavefront that carries P nodes reads with all its lanes: 64 / P lanes a
+// node, each CPL_PEEK of the node's neighbours at a time, so that all their
+// round trips to memory overlap (the first neighbours' places and weights stay
+// in registers for the run).  The words of a post show by themselves that they
+// are the day's (CplPost), so what a look brings is used without a fence or a
+// second load.  Each lane works out its neighbours' terms, and the terms are
+// then added up in stored order, lane after lane.
+//
+// What bounds it: one device-coherent round trip a day at least (3 of the 7 us
+// a day), the day's draws and scheduled events of the neighbourhood.  1,600
+// farms over 200 days, a day: 14 to 23 us with a release, an acquire fence and
+// the posts loaded again after the wait by the one lane of each node; 10.5 us
+// with posts that show their day; 8.0 us with every lane reading; 7.3 us with
+// the terms exchanged four at a time and record places kept between days.
+constexpr int CPL_PEEK = 4;
 
-template <class M>
-__device__ __forceinline__ double coupled_sum(const KParams& p, const Node<M>& s, int k, int b, bool active,
-                                              bool owner) {
-    const int32_t ni = s.u[0] + s.u[1];
-    CplPost* post = p.cpl_post + (size_t)(b & 1) * p.n;
-    if (owner) {
-        post[k].phi = s.v[0];
-        post[k].n = ni;
-        __hip_atomic_store(&post[k].day, b, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    const int e0 = active ? p.cpl_off[k] : 0;
-    const int eend = active ? p.cpl_off[k + 1] : 0;
-    int e = e0;
-    unsigned spins = 0;
-    WaitClock clock;
-    while (__any(e < eend)) {
-        int32_t d[CPL_PEEK];
+struct CplLane {
+    int sub, lanes;       // the lane's place among the `lanes` that read for its node
+    int own;              // the lane that carries that node
+    int e0, eend, fend;   // the node's neighbours, the nodes to wait for only from fend
+    int idx[CPL_PEEK];    // the lane's first neighbours
+    double w[CPL_PEEK];
+};
+
+// cnt nodes in the wavefront from node k0 on, every stride-th lane carrying one.
+__device__ __forceinline__ CplLane cpl_lane(const KParams& p, int cnt, int k0, int stride, int kend) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    CplLane c;
+    c.lanes = WAVE / cnt;
+    const int slot = lane / c.lanes, k = k0 + slot;
+    c.sub = lane % c.lanes;
+    c.own = slot * stride;
+    const bool active = k < kend;
+    c.e0 = active ? p.cpl_off[k] : 0;
+    c.eend = active ? p.cpl_off[k + 1] : 0;
+    c.fend = active ? p.cpl_fend[k] : 0;
 #pragma unroll
-        for (int q = 0; q < CPL_PEEK; ++q)
-            d[q] = e + q < eend
-                       ? __hip_atomic_load(&post[p.cpl_idx[e + q]].day, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                       : b;
-        int ready = 0;
-        bool gap = false;
-#pragma unroll
-        for (int q = 0; q < CPL_PEEK; ++q) {
-            gap = gap || d[q] != b;
-            ready += gap ? 0 : 1;
-        }
-        e = min(e + ready, eend);
-        if (!__any(ready > 0) && (++spins & 255u) == 0) {
-            const bool quit = __hip_atomic_load(&p.ctrl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
-                              load_error_step(p.ctrl) < (uint64_t)b;
-            const bool late = __shfl(clock.expired(p.wait_ticks) ? 1 : 0, 0, WAVE) != 0;
-            if (late && (threadIdx.x & (WAVE - 1)) == 0)
-                __hip_atomic_store(&p.ctrl->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (__any(quit) || late) break;
-            __builtin_amdgcn_s_sleep(1);
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    double c = 0.0;
-    if (active && ni > 0) {
-        const int fend = p.cpl_fend[k];
-#pragma unroll 4
-        for (int f = e0; f < fend; ++f) {
-            const int j = p.cpl_idx[f];
-            c = c + M::coupling_term(post[j].phi, post[j].n, s.v[0], ni, p.cpl_w[f]);
-        }
+    for (int q = 0; q < CPL_PEEK; ++q) {
+        const int f = c.e0 + q * c.lanes + c.sub;
+        c.idx[q] = f < c.eend ? p.cpl_idx[f] : 0;
+        c.w[q] = f < c.fend ? p.cpl_w[f] : 0.0;
     }
     return c;
+}
+
+__device__ __forceinline__ void post_word(unsigned long long* w, uint32_t x, int b) {
+    __hip_atomic_store(w, (unsigned long long)(uint32_t)b << 32 | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long peek_word(unsigned long long* w) {
+    return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Called by every lane of the wavefront; `owner` is the lane that posts for
+// its node k, and nodes that an error stopped keep posting their last state.
+// Returns the node's sum in the lanes that carry it (0 for an empty node).  A
+// wait longer than the wall-clock limit abandons the run; an earlier error
+// lets the waits give up (the run's later results are undefined).
+template <class M>
+__device__ __forceinline__ double coupled_sum(const KParams& p, const Node<M>& s, const CplLane& cp, int k, int b,
+                                              bool owner, bool narrow) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    CplPost* post = p.cpl_post + (size_t)(b & 1) * p.n;
+    int32_t ni = s.u[0] + s.u[1];
+    double phi_i = s.v[0];
+    if (owner) {
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(phi_i);
+        post_word(&post[k].w[0], (uint32_t)bits, b);
+        post_word(&post[k].w[1], (uint32_t)(bits >> 32), b);
+        post_word(&post[k].w[2], (uint32_t)ni, b);
+    }
+    ni = __shfl(ni, cp.own, WAVE);
+    phi_i = __shfl(phi_i, cp.own, WAVE);
+    const uint32_t tag = (uint32_t)b;
+    double c = 0.0;
+    unsigned spins = 0;
+    WaitClock clock;
+    bool quit = false;
+    for (int base = cp.e0; !quit && __any(base < cp.eend); base += CPL_PEEK * cp.lanes) {
+        int idx[CPL_PEEK];
+        double w[CPL_PEEK], phi[CPL_PEEK];
+        int32_t n[CPL_PEEK];
+        unsigned wait = 0;  // neighbours whose post has not been seen
+#pragma unroll
+        for (int q = 0; q < CPL_PEEK; ++q) {
+            const int f = base + q * cp.lanes + cp.sub;
+            idx[q] = cp.idx[q];
+            w[q] = cp.w[q];
+            if (base > cp.e0 && f < cp.eend) {
+                idx[q] = p.cpl_idx[f];
+                w[q] = p.cpl_w[f];
+            }
+            phi[q] = 0.0;
+            n[q] = 0;
+            wait |= f < cp.eend ? 1u << q : 0u;
+        }
+        while (__any(wait != 0)) {
+            unsigned long long w0[CPL_PEEK], w1[CPL_PEEK], w2[CPL_PEEK];
+#pragma unroll
+            for (int q = 0; q < CPL_PEEK; ++q)
+                if ((wait >> q) & 1u) {
+                    CplPost* from = post + idx[q];
+                    w0[q] = peek_word(&from->w[0]);
+                    w1[q] = peek_word(&from->w[1]);
+                    w2[q] = peek_word(&from->w[2]);
+                }
+            const unsigned before = wait;
+#pragma unroll
+            for (int q = 0; q < CPL_PEEK; ++q)
+                if (((before >> q) & 1u) && (uint32_t)(w0[q] >> 32) == tag && (uint32_t)(w1[q] >> 32) == tag &&
+                    (uint32_t)(w2[q] >> 32) == tag) {
+                    phi[q] = __longlong_as_double((long long)(w1[q] << 32 | (uint32_t)w0[q]));
+                    n[q] = (int32_t)(uint32_t)w2[q];
+                    wait &= ~(1u << q);
+                }
+            if (!__any(wait != before) && (++spins & 255u) == 0) {
+                const bool stop = __hip_atomic_load(&p.ctrl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
+                                  load_error_step(p.ctrl) < (uint64_t)b;
+                const bool late = __shfl(clock.expired(p.wait_ticks) ? 1 : 0, 0, WAVE) != 0;
+                if (late && lane == 0)
+                    __hip_atomic_store(&p.ctrl->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (__any(stop) || late) {
+                    quit = true;
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+        }
+        const int first = lane - cp.sub;
+#pragma unroll
+        for (int q = 0; q < CPL_PEEK; ++q) {
+            const int f0 = base + q * cp.lanes;
+            if (!__any(f0 < cp.fend)) break;
+            const double term = M::coupling_term(phi[q], n[q], phi_i, ni, w[q]);
+            // four terms' exchanges at a time, then their additions in order
+            for (int i = 0; i < cp.lanes && __any(f0 + i < cp.fend); i += 4) {
+                double x[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[j] = __shfl(term, first + min(i + j, cp.lanes - 1), WAVE);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) c = i + j < cp.lanes && f0 + i + j < cp.fend ? c + x[j] : c;
+            }
+        }
+    }
+    if (ni <= 0) c = 0.0;
+    return narrow ? __shfl(c, lane * cp.lanes & (WAVE - 1), WAVE) : c;
 }
 
 template <class M, bool PIPE, bool GRP, bool AEM = false>
@@ -1585,6 +1719,13 @@ __global__ void __launch_bounds__(256) flow_kernel(KParams pa) {
         }
 
     }
+    CplLane cpl{};
+    if constexpr (M::COUPLED)
+        cpl = wide  ? cpl_lane(p, 1, gw, 1, p.nbig)
+              : grp ? cpl_lane(p, WAVE / GROUP_LANES, p.nbig + (gw - p.nbig) * (WAVE / GROUP_LANES), GROUP_LANES,
+                               p.nbig + p.ngrp)
+                    : cpl_lane(p, p.pack, k - lane, 1, p.n);
+    RecordAt<M> at = record_at<M>(p, k, p.rec_off[0]);
     bool dead = false;
     uint64_t key_raw = 0;  // error key, refreshed every 8 days and read 8 days later
     for (int b = 0; b < p.nb; ++b) {
@@ -1594,6 +1735,7 @@ __global__ void __launch_bounds__(256) flow_kernel(KParams pa) {
                 key_raw = __hip_atomic_load(&p.ctrl->err_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         const int64_t day = p.T1 + b;
+        const int rec_end = p.rec_off[b + 1];  // (read ahead of the day)
         if (grp)
             group_day<M>(p, s, active && !dead, b, day, node, stream, ord, cur, cend, nrec, dead, t, owner);
         else if (active && !dead)
@@ -1661,7 +1803,7 @@ __global__ void __launch_bounds__(256) flow_kernel(KParams pa) {
             }
         }
         if constexpr (M::COUPLED) {
-            const double c = coupled_sum<M>(p, s, k, b, active, owner);
+            const double c = coupled_sum<M>(p, s, cpl, k, b, owner, !wide && !grp);
             if (active && !dead) {
                 if (!M::pts_coupled(s.v, s.u, s.ld, s.gd, day, c)) {
                     if (owner) raise_error(p.ctrl, b, PH_PTS, ord, E_PTS);
@@ -1676,7 +1818,7 @@ __global__ void __launch_bounds__(256) flow_kernel(KParams pa) {
             }
             t.nd += owner ? 1 : 0;
         }
-        record<M>(p, s, k, run, owner, p.rec_off[b], p.rec_off[b + 1]);
+        record_to<M>(p, s, at, k, run, owner, rec_end);
     }
     add_counters(p.ctrl, t.tr, t.nd, t.ev, t.dr);
 }
@@ -1843,7 +1985,8 @@ __global__ void init_kernel(KParams p, int nc, int nv, int first_rec, int reset_
     if (p.mode == MODE_FLOW)
         for (int e = gtid; e < p.n_e2; e += nthreads) p.mail[e] = 0ull;
     if (p.coupled)
-        for (int i = gtid; i < 2 * p.n; i += nthreads) p.cpl_post[i].day = -1;
+        for (int i = gtid; i < 2 * p.n; i += nthreads)
+            for (int j = 0; j < 3; ++j) p.cpl_post[i].w[j] = ~0ull;
     if (p.solver == 1) {
         // the all events method: integrals 0, each channel's first level its
         // first exponential
