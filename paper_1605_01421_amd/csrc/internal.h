@@ -117,6 +117,9 @@ struct alignas(32) CplPost {
     unsigned long long w[4];  // phi's low half, phi's high half, n; one unused
 };
 
+// Mailbox words of a transfer: three 16-bit counts each.
+__host__ __device__ constexpr int mail_words(int nc) { return (nc + 2) / 3; }
+
 struct KParams {
     int32_t n;        // nodes in the group
     int32_t nb;       // number of unit-time steps
@@ -150,7 +153,7 @@ struct KParams {
     const int4* e2n_rec;         //           packed record of each (sources sample from it)
     const int4* e2n_item;        //           x = event index, y = step, z = role (0 source,
                                  //           1 destination, 2 both), w = run of the event
-    unsigned long long* mail;    // dataflow: [n_e2] counts a transfer delivers (0 = not yet)
+    unsigned long long* mail;    // dataflow: [n_e2][mail_words(Nc)] counts a transfer delivers (0 = not yet)
     int32_t* mail_big;           //           [n_e2][Nc] counts too large to pack
     int32_t n_e2;
     int32_t record;              // 0 full, 1 sums

@@ -1124,7 +1124,7 @@ int create_impl(const siminf_spec* specs, int nspecs, const int32_t* reps, const
         if (g.n_e2 > 0) {
             // live state for the transfer kernels (both variants)
             if (alloc_device(m->owned, (size_t)nc * n, &p.u) || alloc_device(m->owned, (size_t)std::max(nv, 1) * n, &p.v) ||
-                alloc_device(m->owned, (size_t)n, &p.e1_cur) || alloc_device(m->owned, (size_t)p.n_e2, &p.mail) ||
+                alloc_device(m->owned, (size_t)n, &p.e1_cur) || alloc_device(m->owned, (size_t)p.n_e2 * mail_words(nc), &p.mail) ||
                 alloc_device(m->owned, (size_t)p.n_e2 * nc, &p.mail_big))
                 return hip_fail(m);
         }

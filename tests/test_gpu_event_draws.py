@@ -1,0 +1,111 @@
+"""The individuals of an event drawn by many lanes at once and the mailbox
+words of models with more than three compartments: around the sizes at which a
+window of draws or a word ends, with every way a node is carried, against the
+oracle.  States are whole numbers and have to be equal; nothing here has a
+tolerance."""
+import os
+
+import numpy as np
+import pytest
+
+from paper_1605_01421_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+NTHREADS = min(16, os.cpu_count() or 1)
+SIZES = [1, 3, 4, 5, 7, 8, 9, 16, 17, 63, 64, 65, 128, 129, 700]
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    from paper_1605_01421_amd import siminf
+    siminf.load()
+    return siminf
+
+
+def _check(lib, spec, what, solver="ssm", **opts):
+    import oracle
+    print("[gpu]", what, spec.name, opts, flush=True)
+    ref = oracle.run(spec, 11, 2, nthreads=NTHREADS, solver=solver)
+    assert ref["status"] == 0, ref["error"]
+    m = lib.Model(spec, solver=solver, **opts)
+    for _ in range(2):
+        m.run(11, 2)
+        assert m.wait() == 0, m.error_info()
+        U, V = m.trajectory()
+        assert np.array_equal(U, ref["U"])
+        if V.size:
+            assert np.array_equal(V, ref["V"])
+    c = m.counters()
+    assert (c["transitions"], c["events"]) == (ref["transitions"], ref["events"])
+    m.close()
+
+
+def _rows(Nn, days, transfers, every, one, shift):
+    """Events of each size in SIZES on every node in turn, as exits, internal
+    transfers (where there is a shift) and transfers to the next node, and
+    proportions from none to all; select `every` takes several compartments,
+    `one` a single one."""
+    rows = []
+    for i in range(Nn):
+        for d in range(1, days + 1):
+            n = SIZES[(i + d) % len(SIZES)]
+            kind = (i + 3 * d) % 4
+            if kind == 0:
+                rows.append((W.EXIT, d, i, 0, max(n // 8, 1), 0.0, every, -1))
+                rows.append((W.ENTER, d, i, 0, max(n // 8, 1), 0.0, one, -1))
+            elif kind == 1 and shift is not None:
+                rows.append((W.INTTRANS, d, i, 0, 0, (0.0, 0.3, 0.8, 1.0)[d % 4], every, shift))
+            elif kind == 2 and transfers:
+                rows.append((W.EXTTRANS, d, i, (i + 1) % Nn, n, 0.0, every, -1))
+            elif transfers:
+                rows.append((W.EXTTRANS, d, i, (i + 5) % Nn, 0, 0.02, every, -1))
+                if d % 5 == 0:
+                    rows.append((W.EXTTRANS, d, i, (i + 2) % Nn, 0, 1.0, one, -1))
+    return W.make_events(rows)
+
+
+def _sir(Nn, transfers, days=24):
+    rng = np.random.default_rng(Nn)
+    u0 = np.stack([rng.integers(20000, 40000, Nn), rng.integers(0, 30, Nn), rng.integers(0, 500, Nn)], 1)
+    ev = _rows(Nn, days, transfers, 3, 1, None)
+    return W.sir_spec(u0, np.arange(0, days + 1), 0.02, 0.05, events=ev, name="SIR draws")
+
+
+def _five(Nn, days=24, herd=3000, big=0):
+    """S, I, Icum, R, V: five compartments take two mailbox words."""
+    rng = np.random.default_rng(Nn + 1)
+    u0 = np.zeros((Nn, 5), np.int64)
+    u0[:, 0] = rng.integers(20000, 40000, Nn)
+    u0[:, 1] = rng.integers(0, 30, Nn)
+    u0[:, 3] = rng.integers(0, herd, Nn)
+    E = np.array([[1, 1, 1], [0, 1, 1], [0, 0, 0], [0, 1, 1], [0, 1, 0]], np.int32)
+    N = np.array([[4], [3], [0], [1], [0]], np.int32)
+    ev = _rows(Nn, days, True, 1, 0, 0)
+    if big:
+        # counts beyond 16 bits go through the side array
+        u0[:3, 0] += 4 * big
+        more = [(W.EXTTRANS, d, i, i + 1, big + d, 0.0, 1, -1) for d in (2, 9) for i in range(2)]
+        ev = W.concat_events(ev, W.make_events(more))
+    return W.mparse_spec(["S -> b*S*I/(S+I+R+V) -> I + Icum", "I -> g*I -> R"], ["S", "I", "Icum", "R", "V"], u0,
+                         np.arange(0, days + 1), gdata=dict(b=0.02, g=0.05), E=E, N=N, events=ev, name="five draws")
+
+
+@pytest.mark.parametrize("transfers", [False, True])
+@pytest.mark.parametrize("opts", [dict(), dict(lanes=64, wide=200), dict(lanes=1, group=-1), dict(lanes=1),
+                                  dict(lanes=1, pack=4), dict(lanes=64, wide=9, group=40, pack=8),
+                                  dict(lanes=64, wide=70, lattice=2), dict(mode=1)])
+def test_sir(lib, transfers, opts):
+    _check(lib, _sir(150, transfers), f"transfers {transfers}", **opts)
+
+
+@pytest.mark.parametrize("Nn,big", [(7, 0), (130, 0), (130, 0xFFF0)])
+def test_five_compartments(lib, Nn, big):
+    for opts in (dict(), dict(pack=64), dict(mode=1)):
+        _check(lib, _five(Nn, big=big), f"{Nn} nodes, big {big}", **opts)
+
+
+def test_no_transfers_on_lanes_of_a_queue(lib):
+    _check(lib, _sir(300, False), "lane queue", lane_queue=1)
