@@ -1,8 +1,8 @@
-"""The individuals of an event drawn by many lanes at once and the mailbox
-words of models with more than three compartments: around the sizes at which a
-window of draws or a word ends, with every way a node is carried, against the
-oracle.  States are whole numbers and have to be equal; nothing here has a
-tolerance."""
+"""The individuals of an event drawn by many lanes at once, the mailbox words
+of models with more than three compartments, and the exponentials of the all
+events method made ahead: around the sizes at which a window of draws, a word
+or a lane's share ends, with every way a node is carried, against the oracle.
+States are whole numbers and have to be equal; nothing here has a tolerance."""
 import os
 
 import numpy as np
@@ -109,3 +109,20 @@ def test_five_compartments(lib, Nn, big):
 
 def test_no_transfers_on_lanes_of_a_queue(lib):
     _check(lib, _sir(300, False), "lane queue", lane_queue=1)
+
+
+@pytest.mark.parametrize("pack", [0, 4, 8, 16, 32, 64])
+def test_all_events_method(lib, pack):
+    """Two channels (up to 8 exponentials ahead of each) and five (3 ahead at
+    4 nodes a wavefront, none at more), with few and with many steps a day,
+    nodes past a whole wavefront and a last one that is nearly empty."""
+    Nn = 131
+    rng = np.random.default_rng(4)
+    u0 = np.stack([rng.integers(0, 400, Nn), rng.integers(0, 40, Nn), np.zeros(Nn, int)], 1)
+    _check(lib, W.sir_spec(u0, np.arange(0, 31), 0.4, 0.2), "SIR", "aem", pack=pack)
+    spec = W.sir_with_events(seed=3, Nn=Nn, days=30)
+    _check(lib, spec, "SIR, transfers", "aem", pack=pack)
+    tr = ["S -> b*S*I/(S+E+I+R+1) -> E", "E -> 0.7*E -> I", "I -> g*I -> R", "R -> w*R -> S", "S -> 0.01*S -> R"]
+    u5 = np.concatenate([u0[:, :1], np.zeros((Nn, 1), int), u0[:, 1:]], 1)
+    _check(lib, W.mparse_spec(tr, ["S", "E", "I", "R"], u5, np.arange(0, 31), gdata=dict(b=0.5, g=0.2, w=0.05),
+                              name="SEIRS"), "five channels", "aem", pack=pack)
