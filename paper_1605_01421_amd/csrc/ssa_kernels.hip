@@ -1979,6 +1979,102 @@ __device__ __forceinline__ double coupled_sum(const KParams& p, const Node<M>& s
     return narrow ? __shfl(c, lane * cp.lanes & (WAVE - 1), WAVE) : c;
 }
 
+// A transfer of a node: its index e, its step and, in one register, the node's
+// role in it (1: it arrives, 0: the node sends it, 2: to itself) above the
+// stream (of which 24 bits count).
+struct E2Item {
+    int e, step;
+    uint32_t role_stream;
+    __device__ __forceinline__ uint32_t role() const { return role_stream >> 30; }
+};
+__device__ __forceinline__ E2Item e2_item(const KParams& p, int at) {
+    const int4 x = p.e2n_item[at];
+    return {x.x, x.y, (uint32_t)x.z << 30 | ((p.stream_base + (uint32_t)x.w) & 0xFFFFFFu)};
+}
+
+// The lanes' window of a node's transfers (every lane of the group loads one;
+// past the end one that is never due).
+template <int G>
+__device__ __forceinline__ void e2_window(const KParams& p, int tcur, int tend, E2Item& item, int4& trec, int& tbase) {
+    const int at = tcur + (int)(threadIdx.x & (WAVE - 1)) % G;
+    tbase = tcur;
+    item = {0, NO_STEP, 0u};
+    if (at < tend) {
+        item = e2_item(p, at);
+        trec = p.e2n_rec[at];
+    }
+}
+// A lane's x, read by every lane of its group.
+template <int G>
+__device__ __forceinline__ int group_int(int x, int gb, int j) {
+    if constexpr (G == WAVE)
+        return __builtin_amdgcn_readlane(x, __builtin_amdgcn_readfirstlane(j));
+    else
+        return __shfl(x, gb + j, WAVE);
+}
+
+// The next transfers of step b of a node that G lanes carry, as far as they
+// can go without waiting: the arrivals up to the next transfer that the node
+// sends or that has not been posted, then that one if the node sends it.
+// Counts that arrive are only added, so their order among themselves does not
+// matter: each lane looks into its own transfer's mailbox, and a run of them
+// costs one trip to memory instead of two each.  Called by every lane of the
+// groups with a transfer due; returns whether any was made.  due: the step of
+// the node's next transfer.  SISe, 37,000 herds over 365 days: 13.0 ms with a
+// herd that gets 30 movements a day one by one, 7.0 so; 65 and 32.5 ms with one
+// that gets 158; 2.8 either way where none gets more than 3.
+template <class M, int G>
+__device__ __forceinline__ bool e2_lanes(const KParams& p, Node<M>& s, int b, E2Item& item, int4& trec, int& tcur,
+                                         int& tbase, int tend, int& due, bool owner, bool& dead, Tally& t) {
+    const int lane = threadIdx.x & (WAVE - 1), gl = lane % G, gb = lane - gl;
+    const int from = tcur - tbase;
+    const bool mine = gl >= from && item.step == b;
+    const int send = first_bit<G>(group_bits<G>(mine && item.role() != 1, gb));
+    const bool arrives = mine && item.role() == 1 && gl < send;
+    int32_t cnt[M::NC];
+#pragma unroll
+    for (int c = 0; c < M::NC; ++c) cnt[c] = 0;
+    const bool here = arrives && take_mail<M::NC>(p, item.e, cnt);
+    int to = min(first_bit<G>(group_bits<G>(arrives && !here, gb)),
+                 from + bits_below<G>(group_bits<G>(arrives, gb), G));
+    if (some_group<G>(to > from)) {
+#pragma unroll
+        for (int c = 0; c < M::NC; ++c) {
+            int x = gl < to ? cnt[c] : 0;
+#pragma unroll
+            for (int d = 1; d < G; d *= 2) x += __shfl_xor(x, d, WAVE);
+            s.u[c] += x;
+        }
+    }
+    if (to == send && send < G) {
+        const int e = group_int<G>(item.e, gb, send);
+        const uint32_t stream = (uint32_t)group_int<G>((int)item.role_stream, gb, send);
+        const int4 rec = make_int4(group_int<G>(trec.x, gb, send), group_int<G>(trec.y, gb, send),
+                                   group_int<G>(trec.z, gb, send), group_int<G>(trec.w, gb, send));
+        int32_t got[M::NC];
+#pragma unroll
+        for (int c = 0; c < M::NC; ++c) got[c] = 0;
+        const int rc = dead ? 0 : apply_event<M, G>(rec, p.e2.prop, e, p.seed, stream, s.u, got);
+        if (rc) {
+            if (owner) raise_error(p.ctrl, b, PH_E2, p.e2.ordinal[e], rc);
+            dead = true;
+        }
+        if (stream >> 30 == 2) {
+#pragma unroll
+            for (int c = 0; c < M::NC; ++c) s.u[c] += got[c];
+        } else if (owner) {
+            post_mail<M::NC>(p, e, got);
+        }
+        t.ev += (owner && !rc && !dead) ? 1 : 0;
+        ++to;
+    }
+    if (to == from) return false;
+    tcur = tbase + to;
+    if (to == G) e2_window<G>(p, tcur, tend, item, trec, tbase);
+    due = group_int<G>(item.step, gb, tcur - tbase);
+    return true;
+}
+
 template <class M, bool PIPE, bool GRP, bool AEM = false>
 __global__ void __launch_bounds__(256) flow_kernel(KParams pa) {
     KParams p = pa;
@@ -2004,8 +2100,9 @@ __global__ void __launch_bounds__(256) flow_kernel(KParams pa) {
     int run = 0, cur = 0, cend = 0, tcur = 0, tend = 0;
     uint32_t node = 0, stream = 0;
     int64_t ord = 0;
-    int4 nrec = make_int4(0, 0, 0, 0), item = make_int4(0, NO_STEP, 0, 0), trec = make_int4(0, 0, 0, 0);
-    int wbase = 0;
+    int4 nrec = make_int4(0, 0, 0, 0), trec = make_int4(0, 0, 0, 0);
+    E2Item item{0, NO_STEP, 0u};
+    int wbase = 0, tbase = 0, due = NO_STEP;  // due: the step of the node's next transfer
     AemState<M, AEM> a{};
     if (active) {
         load_node<M>(p, k, s, run, node, stream, ord, cur, cend, nrec, wide, wbase);
@@ -2013,10 +2110,14 @@ __global__ void __launch_bounds__(256) flow_kernel(KParams pa) {
         tcur = p.e2n_off[k];
         tend = p.e2n_off[k + 1];
         if (tcur < tend) {
-            item = p.e2n_item[tcur];
+            item = e2_item(p, tcur);
             trec = p.e2n_rec[tcur];
         }
-
+        due = item.step;
+        if (wide)
+            e2_window<WAVE>(p, tcur, tend, item, trec, tbase);
+        else if (grp)
+            e2_window<GROUP_LANES>(p, tcur, tend, item, trec, tbase);
     }
     CplLane cpl{};
     if constexpr (M::COUPLED)
@@ -2044,57 +2145,56 @@ __global__ void __launch_bounds__(256) flow_kernel(KParams pa) {
         // this step's external transfers of the node, in key order.  The loop
         // is uniform over the wavefront and every lane that can move on does:
         // sources never wait, so no lane can block another one of its wave.
-        bool pending = active && item.y == b;
+        bool pending = active && due == b;
         unsigned spins = 0;
         WaitClock clock;
         while (__any(pending)) {
             bool moved = false;
-            const int e = item.x;
-            const bool source = pending && item.z != 1;
-            // sources (or sources and destinations): sample
-            int32_t got[M::NC];
-#pragma unroll
-            for (int c = 0; c < M::NC; ++c) got[c] = 0;
-            const uint32_t ev_stream = p.stream_base + (uint32_t)item.w;
-            int rc = 0;
             if (wide || grp) {
                 if constexpr (!AEM && !M::GENERATED) {
-                    if (source && !dead)
-                        rc = wide ? apply_event<M, WAVE>(trec, p.e2.prop, e, p.seed, ev_stream, s.u, got)
-                                  : apply_event<M, GROUP_LANES>(trec, p.e2.prop, e, p.seed, ev_stream, s.u, got);
+                    if (pending)
+                        moved = wide ? e2_lanes<M, WAVE>(p, s, b, item, trec, tcur, tbase, tend, due, owner, dead, t)
+                                     : e2_lanes<M, GROUP_LANES>(p, s, b, item, trec, tcur, tbase, tend, due, owner,
+                                                                dead, t);
                 }
             } else {
-                rc = apply_events<M>(source && !dead, trec, p.e2.prop, e, p.seed, ev_stream, s.u, got);
-            }
-            if (pending) {
+                const int e = item.e;
+                const bool source = pending && item.role() != 1;
+                // sources (or sources and destinations): sample
+                int32_t got[M::NC];
+#pragma unroll
+                for (int c = 0; c < M::NC; ++c) got[c] = 0;
+                const int rc = apply_events<M>(source && !dead, trec, p.e2.prop, e, p.seed, item.role_stream,
+                                               s.u, got);
                 if (source) {
                     // and post
                     if (rc) {
-                        if (owner) raise_error(p.ctrl, b, PH_E2, p.e2.ordinal[e], rc);
+                        raise_error(p.ctrl, b, PH_E2, p.e2.ordinal[e], rc);
                         dead = true;
                     }
-                    if (item.z == 2) {
+                    if (item.role() == 2) {
 #pragma unroll
                         for (int c = 0; c < M::NC; ++c) s.u[c] += got[c];
-                    } else if (owner) {
+                    } else {
                         post_mail<M::NC>(p, e, got);
                     }
-                    t.ev += (owner && !rc && !dead) ? 1 : 0;
+                    t.ev += (!rc && !dead) ? 1 : 0;
                     moved = true;
-                } else {
+                } else if (pending) {
                     moved = take_mail<M::NC>(p, e, s.u);
                 }
                 if (moved) {
                     ++tcur;
                     if (tcur < tend) {
-                        item = p.e2n_item[tcur];
+                        item = e2_item(p, tcur);
                         trec = p.e2n_rec[tcur];
                     } else {
-                        item.y = NO_STEP;
+                        item.step = NO_STEP;
                     }
+                    due = item.step;
                 }
-                pending = item.y == b;
             }
+            pending = active && due == b;
             if (!__any(moved)) {
                 if ((++spins & 255u) == 0) {
                     const bool quit = __hip_atomic_load(&p.ctrl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||

@@ -1,8 +1,9 @@
 """The individuals of an event drawn by many lanes at once, the mailbox words
-of models with more than three compartments, and the exponentials of the all
-events method made ahead: around the sizes at which a window of draws, a word
-or a lane's share ends, with every way a node is carried, against the oracle.
-States are whole numbers and have to be equal; nothing here has a tolerance."""
+of models with more than three compartments, a node's arrivals taken by the
+lanes that carry it, and the exponentials of the all events method made ahead:
+around the sizes at which a window of draws or arrivals, a word or a lane's
+share ends, with every way a node is carried, against the oracle.  States are
+whole numbers and have to be equal; nothing here has a tolerance."""
 import os
 
 import numpy as np
@@ -109,6 +110,31 @@ def test_five_compartments(lib, Nn, big):
 
 def test_no_transfers_on_lanes_of_a_queue(lib):
     _check(lib, _sir(300, False), "lane queue", lane_queue=1)
+
+
+def _hub(Nn, days=12):
+    """Every node ships to node 0 every day, node 0 to a few and some node to
+    itself, in any order: node 0's arrivals fill a window of lanes, or several,
+    with transfers it sends in between, before the first and after the last."""
+    rng = np.random.default_rng(Nn)
+    u0 = np.stack([rng.integers(300, 900, Nn), rng.integers(0, 9, Nn), np.zeros(Nn, int)], 1)
+    rows = []
+    for d in range(1, days + 1):
+        today = [(W.EXTTRANS, d, i, 0, int(rng.integers(1, 9)), 0.0, 3, -1) for i in range(1, Nn)]
+        today += [(W.EXTTRANS, d, 0, int(rng.integers(1, Nn)), int(rng.integers(1, 30)), 0.0, 3, -1)
+                  for _ in range(d % 6)]
+        if d % 3 == 0:
+            at = int(rng.integers(0, Nn))
+            today.append((W.EXTTRANS, d, at, at, 4, 0.0, 3, -1))
+        rows += [today[i] for i in rng.permutation(len(today))]
+    return W.sir_spec(u0, np.arange(0, days + 1), 0.1, 0.05, events=W.make_events(rows), name="hub")
+
+
+@pytest.mark.parametrize("Nn", [2, 9, 10, 64, 65, 66, 200])
+def test_hub(lib, Nn):
+    for opts in (dict(), dict(lanes=64, wide=Nn), dict(lanes=1, group=-1), dict(lanes=64, wide=1, group=Nn // 2),
+                 dict(lanes=1, pack=4), dict(mode=1)):
+        _check(lib, _hub(Nn), f"{Nn} nodes", **opts)
 
 
 @pytest.mark.parametrize("pack", [0, 4, 8, 16, 32, 64])
