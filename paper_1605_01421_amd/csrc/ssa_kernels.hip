@@ -843,6 +843,17 @@ __device__ __forceinline__ void record(const KParams& p, const Node<M>& s, int k
     }
 }
 
+// rec_off[i] through the scalar cache: a load that may alias the records would
+// be a vector load, and waiting for it waits for the records of the day before.
+__device__ __forceinline__ int record_end(const KParams& p, int i) {
+    return ((const __attribute__((address_space(4))) int32_t*)p.rec_off)[i];
+}
+// Whether lane 0's error key lies before step b (the step is in bits 44 up);
+// known to be uniform, so that the loops over the days run on the scalar unit.
+__device__ __forceinline__ bool error_before(uint64_t key, int b) {
+    return __builtin_amdgcn_readfirstlane((uint32_t)(key >> 32)) >> 12 < (uint32_t)b;
+}
+
 // Where a lane that writes full records puts the next one of its node: the
 // records of a node are a fixed distance apart, so the places follow from one
 // another by additions.
@@ -1307,7 +1318,7 @@ __global__ void __launch_bounds__(256) free_kernel(KParams pa) {
     for (;;) {
         unsigned chunk = 0;
         if (lane == 0) chunk = atomicAdd(&p.ctrl->work[p.group], 1u);
-        chunk = __shfl(chunk, 0, WAVE);
+        chunk = __builtin_amdgcn_readfirstlane(chunk);
         if (chunk >= (unsigned)p.nchunks) break;
         // chunks [0, nbig): one heavy node per wavefront; then ngw chunks of
         // WAVE / GROUP_LANES nodes with GROUP_LANES lanes each; then pack nodes per chunk
@@ -1333,15 +1344,15 @@ __global__ void __launch_bounds__(256) free_kernel(KParams pa) {
 
         bool dead = false;
         uint64_t key_raw = 0;  // error key, refreshed every 8 days and read 8 days later
-        RecordAt<M> at = record_at<M>(p, k, p.rec_off[0]);
+        RecordAt<M> at = record_at<M>(p, k, record_end(p, 0));
         for (int b = 0; b < p.nb; ++b) {
             if ((b & 7) == 0) {
-                if (b > 0 && (__shfl(key_raw, 0, WAVE) >> 44) < (uint64_t)b) break;
+                if (b > 0 && error_before(key_raw, b)) break;
                 if (lane == 0)
                     key_raw = __hip_atomic_load(&p.ctrl->err_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             const int64_t day = p.T1 + b;
-            const int rec_end = p.rec_off[b + 1];  // (read ahead of the day)
+            const int rec_end = record_end(p, b + 1);  // (read ahead of the day)
             const bool was = active && !dead;  // a node-day begun
             if (grp)
                 group_day<M>(p, s, was, b, day, node, stream, ord, cur, cend, nrec, dead, t, owner);
@@ -1516,7 +1527,7 @@ __device__ __forceinline__ void lane_heavy(const KParams& pa, int k, const int* 
     uint64_t key_raw = 0;  // error key, refreshed every 8 days and read 8 days later
     for (int b = 0; b < p.nb && !dead; ++b) {
         if ((b & 7) == 0) {
-            if (b > 0 && (__shfl(key_raw, 0, WAVE) >> 44) < (uint64_t)b) break;
+            if (b > 0 && error_before(key_raw, b)) break;
             if (lane == 0)
                 key_raw = __hip_atomic_load(&p.ctrl->err_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -2085,7 +2096,7 @@ __global__ void __launch_bounds__(256) flow_kernel(KParams pa) {
     const int wpb = blockDim.x / WAVE;
     const int line_g = 32 / (p.pack * wpb);  // workgroups whose records fill one 128-byte line
     const int gw = xcd_block(blockIdx.x, (p.nbig + p.ngw + wpb - 1) / wpb, gridDim.x, line_g) * wpb +
-                   (int)(threadIdx.x / WAVE);
+                   __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     // waves [0, nbig): one heavy node per wavefront
     const bool wide = gw < p.nbig;
     // then ngw waves of WAVE / GROUP_LANES nodes with GROUP_LANES lanes each
@@ -2125,17 +2136,17 @@ __global__ void __launch_bounds__(256) flow_kernel(KParams pa) {
               : grp ? cpl_lane(p, WAVE / GROUP_LANES, p.nbig + (gw - p.nbig) * (WAVE / GROUP_LANES), GROUP_LANES,
                                p.nbig + p.ngrp)
                     : cpl_lane(p, p.pack, k - lane, 1, p.n);
-    RecordAt<M> at = record_at<M>(p, k, p.rec_off[0]);
+    RecordAt<M> at = record_at<M>(p, k, record_end(p, 0));
     bool dead = false;
     uint64_t key_raw = 0;  // error key, refreshed every 8 days and read 8 days later
     for (int b = 0; b < p.nb; ++b) {
         if ((b & 7) == 0) {
-            if (b > 0 && (__shfl(key_raw, 0, WAVE) >> 44) < (uint64_t)b) break;
+            if (b > 0 && error_before(key_raw, b)) break;
             if (lane == 0)
                 key_raw = __hip_atomic_load(&p.ctrl->err_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         const int64_t day = p.T1 + b;
-        const int rec_end = p.rec_off[b + 1];  // (read ahead of the day)
+        const int rec_end = record_end(p, b + 1);  // (read ahead of the day)
         if (grp)
             group_day<M>(p, s, active && !dead, b, day, node, stream, ord, cur, cend, nrec, dead, t, owner);
         else
