@@ -424,9 +424,9 @@ int siminf_launch_info(const siminf_model *m, int32_t out[12]);
  * wide-node choices again with it; then (with group = 0) groups of lanes for
  * the heaviest eighth, quarter or half of the nodes after the wide ones, or
  * for all of them, each with the packing chosen so far and with 16 and 8
- * nodes per one-lane wavefront, and finally the other pipelining setting on
- * the best shape.  Every shape gives bit-identical results;
- * the handle's recorded results are overwritten.  With the environment
+ * nodes per one-lane wavefront, the other pipelining setting on the best
+ * shape, and finally the shape that the model was created with.  Every shape
+ * gives bit-identical results; the handle's recorded results are overwritten.  With the environment
  * variable SIMINF_AUTOTUNE_LOG set (and not "0"), each candidate's time is
  * printed to stderr as it is measured. */
 int siminf_autotune(siminf_model *m, uint64_t seed, int32_t repeats, void *hip_stream, double *best_ms);
